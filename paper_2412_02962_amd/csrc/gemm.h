@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "gn_merge.h"
+#include "kernels.h"
 
 namespace pcpp {
 
@@ -80,16 +81,25 @@ struct GemmParams {
     int64_t xa_ldkv = 0;
     // Set by launch_gemm for a split launch.
     int32_t splitk = 1, n_xcd = 1, tpx = 0, n_tiles = 0;
+    int32_t m_major = 0;  // wide tiles: all W tiles of one token tile together
 };
 constexpr int GEMM_GN_MAXC = 1280;
 constexpr int GEMM_XA_MAXT = 96;  // keys of the cross-attention epilogue
 
 // Bytes of split-K workspace a GEMM of this shape can use (0: it runs
 // unsplit); counters come first, at most GEMM_SPLIT_COUNTERS ints.  conv:
-// the implicit convolution (128 x 128 tiles), else a plain bf16 GEMM (64 x 64
-// tiles; GEGLU and fp32 X never split).
+// the implicit convolution (wide tiles only), else a plain bf16 GEMM (GEGLU
+// and fp32 X never split).
 constexpr int GEMM_SPLIT_COUNTERS = 4096;
 size_t gemm_split_ws_bytes(int M, int N, int K, bool conv = true);
+
+// Wide tiles (gemm_wide.hip).  plan_wide picks the tile and the split of K
+// that are estimated fastest for p, sets p's launch fields and `shape`, and
+// returns true if the estimate lies under limit_us; wide_split_bytes: the
+// most workspace such a plan of a product of these sizes can use.
+bool plan_wide(GemmParams& p, const DeviceLayout& dl, double limit_us, int& shape);
+size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl);
+hipError_t launch_gemm_wide(const GemmParams& p, int shape, hipStream_t s);
 
 bool gemm_shape_ok(const GemmParams& p);
 hipError_t launch_gemm(const GemmParams& p, hipStream_t s);

@@ -14,6 +14,7 @@
 #include <math.h>
 
 #include "common.h"
+#include "gelu.h"
 #include "gemm.h"
 #include "kernels.h"
 
@@ -23,24 +24,6 @@ namespace {
 
 constexpr int BK = 32;
 constexpr int LSTR = 40;  // LDS row stride in elements
-
-// erf by Abramowitz and Stegun, Handbook of Mathematical Functions, formula
-// 7.1.26: erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x) for
-// x >= 0, odd extension; absolute error at most 1.5e-7, far below the bf16
-// rounding of the products it feeds.
-__device__ __forceinline__ float erf_as(float x) {
-    const float a = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, a, 1.0f));
-    float y = __builtin_fmaf(1.061405429f, t, -1.453152027f);
-    y = __builtin_fmaf(y, t, 1.421413741f);
-    y = __builtin_fmaf(y, t, -0.284496736f);
-    y = __builtin_fmaf(y, t, 0.254829592f);
-    y *= t;
-    const float e = __builtin_amdgcn_exp2f(-a * a * 1.4426950408889634f);
-    return copysignf(__builtin_fmaf(-y, e, 1.0f), x);
-}
-
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erf_as(x * 0.70710678118654752f)); }
 
 typedef const __attribute__((address_space(1))) u32x4* gchunk;
 
@@ -290,12 +273,12 @@ static_assert(2 * GEMM_GN_MAXC >= 3 * 256, "the merge scratch fits the scale and
 // AMODE 1 applies GroupNorm to X in its LDS stage: after the products of
 // k-tile kt every lane rewrites the pieces of k-tile kt + 1 its own direct
 // loads brought, published by the next barrier.
-template <int BM, int BN, int NS, bool GEGLU, bool CONV, int AMODE>
+template <int BM, int BN, int NS, bool CONV, int AMODE>
 __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx, const int by, char* lds,
                                               float* gn_tab) {
     constexpr bool AGN = AMODE == 1;
     constexpr bool XATT = AMODE == 2;
-    static_assert(!(AGN || XATT) || (BM == 64 && BN == 64 && !GEGLU && !CONV), "plain 64 x 64 tiles only");
+    static_assert(!(AGN || XATT) || (BM == 64 && BN == 64 && !CONV), "plain 64 x 64 tiles only");
     constexpr int WMB = BM / 64;                      // 32-token blocks per wavefront
     constexpr int WNB = BN / 64;                      // 32-row W blocks per wavefront
     constexpr int XP = BM / 32;                       // 1 KB X pieces per wavefront per k-tile
@@ -304,7 +287,6 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     constexpr int STAGE = (BM + BN) * DBK * 2;        // bytes per stage
     constexpr int NOPS = WNB + WMB;                   // operand reads per k-step
     static_assert((NS - 2) * PT <= 63, "vmcnt holds at most 63 loads");
-    static_assert(!GEGLU || WNB == 2, "GEGLU pairs a value block with a gate block");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -313,7 +295,6 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     const int wn = wave >> 1;
     const int col = lane & 31;
     const int half = lane >> 5;
-    const int bn_out = GEGLU ? BN / 2 : BN;
     // XCD-contiguous tiles (tpx > 0; always with split K): workgroup w runs
     // on XCD w % n_xcd; the tiles of an XCD are a contiguous range of tpx
     // tiles in n-major order (all token tiles of one W tile together), and
@@ -332,7 +313,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         m_tile = tile - n_tile * mt;
     }
     const int m0 = m_tile * BM;
-    const int n0 = n_tile * bn_out;
+    const int n0 = n_tile * BN;
     const int nk_all = p.K / DBK;
     const int kt0 = (int)((int64_t)nk_all * piece / p.splitk);
     const int kt1 = (int)((int64_t)nk_all * (piece + 1) / p.splitk);
@@ -374,7 +355,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     // BN rows never straddle two of them).
     const __bf16* wmat = p.w;
     int wrow0 = n0;
-    if (!GEGLU && p.w_seg_rows > 0) {
+    if (p.w_seg_rows > 0) {
         const int j = n0 / p.w_seg_rows;
         wmat = p.w_seg[j];
         wrow0 = n0 - j * p.w_seg_rows;
@@ -382,9 +363,8 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
 #pragma unroll
     for (int i = 0; i < WP; ++i) {
         const int r = 8 * (wave + 4 * i) + (lane >> 3);
-        const int wr = GEGLU ? (r < BN / 2 ? n0 + r : p.F + n0 + (r - BN / 2)) : wrow0 + r;
         const int c = (lane & 7) ^ ((r >> 1) & 7);
-        wsrc[i] = (const char*)wmat + ((int64_t)wr * p.K + 8 * c) * 2;
+        wsrc[i] = (const char*)wmat + ((int64_t)(wrow0 + r) * p.K + 8 * c) * 2;
     }
     auto issue = [&](int kt, int stage) {
         char* st = lds + stage * STAGE;
@@ -418,10 +398,9 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     uint32_t chunk_off[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) chunk_off[kk] = ((2 * kk + half) ^ cmask) << 4;
-    // W rows of block i: value/gate pairing for GEGLU, else contiguous per wavefront.
-    const uint32_t w_row0 = BM * 128 + (GEGLU ? 32 * wn : (BN / 2) * wn) * 128 + col * 128;
+    const uint32_t w_row0 = BM * 128 + (BN / 2) * wn * 128 + col * 128;
     const uint32_t x_row0 = ((BM / 2) * wm + col) * 128;
-    constexpr int W_BLOCK_STRIDE = GEGLU ? (BN / 2) * 128 : 32 * 128;
+    constexpr int W_BLOCK_STRIDE = 32 * 128;
 
     struct Ops {
         u32x4 w[WNB];
@@ -737,28 +716,21 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     // be the residual buffer itself (an in-place update, each element read
     // and written by the same lane), so the compiler could not move a load
     // above an earlier store.
-    constexpr int NBO = GEGLU ? 1 : WNB;
     auto n_of = [&](int i, int c) {
-        return n0 + (GEGLU ? 32 * wn + 8 * c + 4 * half : (BN / 2) * wn + 32 * i + 8 * c + 4 * half);
+        return n0 + (BN / 2) * wn + 32 * i + 8 * c + 4 * half;
     };
     auto m_of = [&](int j) { return m0 + (BM / 2) * wm + 32 * j + col; };
-    float bias_v[NBO][4][4], bias_g[4][4];
-    f32x4 res_v[NBO][WMB][4];
+    float bias_v[WNB][4][4];
+    f32x4 res_v[WNB][WMB][4];
 #pragma unroll
-    for (int i = 0; i < NBO; ++i)
+    for (int i = 0; i < WNB; ++i)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int n = n_of(i, c);
-            bf16x4 bv = {}, bg = {};
-            if (p.bias != nullptr) {
-                bv = *(const bf16x4*)(p.bias + n);
-                if constexpr (GEGLU) bg = *(const bf16x4*)(p.bias + p.F + n);
-            }
+            bf16x4 bv = {};
+            if (p.bias != nullptr) bv = *(const bf16x4*)(p.bias + n);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                bias_v[i][c][e] = bf16_to_f32(bv[e]);
-                if constexpr (GEGLU) bias_g[c][e] = bf16_to_f32(bg[e]);
-            }
+            for (int e = 0; e < 4; ++e) bias_v[i][c][e] = bf16_to_f32(bv[e]);
 #pragma unroll
             for (int j = 0; j < WMB; ++j) {
                 const int m = min(m_of(j), p.M - 1);
@@ -781,7 +753,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
             }
         }
 #pragma unroll
-    for (int i = 0; i < NBO; ++i) {
+    for (int i = 0; i < WNB; ++i) {
 #pragma unroll
         for (int j = 0; j < WMB; ++j) {
             const int m = m_of(j);
@@ -792,10 +764,6 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
                 float v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * c + e] + bias_v[i][c][e];
-                if constexpr (GEGLU) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] *= gelu_erf(acc[1][j][4 * c + e] + bias_g[c][e]);
-                }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += res_v[i][j][c][e];
                 const int seg = n / p.seg;
@@ -819,11 +787,11 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     }
 }
 
-template <int BM, int BN, int NS, bool GEGLU, bool CONV, int AMODE>
+template <int BM, int BN, int NS, bool CONV, int AMODE>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
     __shared__ __attribute__((aligned(16))) float gn_tab[AMODE == 1 ? GN_TAB_FLOATS : AMODE == 2 ? XA_TAB_FLOATS : 4];
-    gemm_dma_body<BM, BN, NS, GEGLU, CONV, AMODE>(p, blockIdx.x, blockIdx.y, lds, gn_tab);
+    gemm_dma_body<BM, BN, NS, CONV, AMODE>(p, blockIdx.x, blockIdx.y, lds, gn_tab);
 }
 
 // Two independent plain products in one launch (so that neither pays a
@@ -842,9 +810,9 @@ __global__ __launch_bounds__(256) void gemm_dma_pair_kernel(GemmPair pp) {
     __shared__ __attribute__((aligned(16))) float gn_tab[AMODE_A == 1 ? GN_TAB_FLOATS : 4];
     const int id = blockIdx.x;
     if (id < pp.n_a)
-        gemm_dma_body<BM, BN, NS, false, false, AMODE_A>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, gn_tab);
+        gemm_dma_body<BM, BN, NS, false, AMODE_A>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, gn_tab);
     else if (id >= pp.b0)
-        gemm_dma_body<BM, BN, NS, false, false, 0>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, gn_tab);
+        gemm_dma_body<BM, BN, NS, false, 0>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, gn_tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -1015,223 +983,18 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// GEGLU on balanced tiles: BM tokens x 160 outputs (their 160 value rows and
-// 160 gate rows of W) per workgroup, so that the block's 2048 x 2560 product
-// (BM = 128) and the level-2 512 x 5120 product (BM = 64) are 256 tiles, one
-// per compute unit.  16x16x32 MFMAs, Y^T = W X^T; eight wavefronts, each
-// holding the value and the gate of the same outputs, so the GELU product is
-// formed in registers.  BM = 128: wavefront w takes tokens 32 (w % 4) .. + 31
-// and outputs 80 (w / 4) .. + 79.  BM = 64: wavefront w takes tokens
-// 32 (w % 2) .. + 31, outputs 80 ((w / 2) % 2) .. + 79 and k-step w / 4 of
-// the two 32-long steps of each k-tile; the two k-steps' sums meet through
-// LDS at the end.  LDS stage: X rows, then value rows, then gate rows, 128
-// bytes each (the swizzle above): 448 rows (56 KB, two stages) or 384 rows
-// (48 KB, three stages); 1 KB direct-load pieces, the same number per
-// wavefront.  With tpx > 0 the tiles run in XCD-contiguous n-major order (W
-// at least four times X: a W tile is then fetched into one XCD's L2).
-// ---------------------------------------------------------------------------
-constexpr int GG_BN = 160;
-
-template <int GBM>
-struct GegluShape {
-    static constexpr int ROWS = GBM + 2 * GG_BN;
-    static constexpr int STAGE = ROWS * DBK * 2;
-    static constexpr int NS = GBM == 128 ? 2 : 3;
-    static constexpr int PT = ROWS / 8 / 8;  // pieces per wavefront per k-tile
-    static constexpr bool KSPLIT = GBM == 64;
-};
-
-template <int GBM>
-__global__ __launch_bounds__(512) void geglu160_kernel(GemmParams p) {
-    using SH = GegluShape<GBM>;
-    __shared__ __attribute__((aligned(16))) char lds[SH::NS * SH::STAGE];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tb = SH::KSPLIT ? (wave & 1) : (wave & 3);
-    const int vg = SH::KSPLIT ? ((wave >> 1) & 1) : (wave >> 2);
-    const int kg = SH::KSPLIT ? (wave >> 2) : 0;
-    int m_tile = blockIdx.x, n_tile = blockIdx.y;
-    if (p.tpx > 0) {  // XCD-contiguous: workgroup w on XCD w % n_xcd, n-major within an XCD
-        const int xcd = blockIdx.x % p.n_xcd;
-        const int tl = blockIdx.x / p.n_xcd;
-        const int tile = xcd * p.tpx + tl;
-        if (tl >= p.tpx || tile >= p.n_tiles) return;  // idle slot of the last XCD (uniform)
-        const int mt = (p.M + GBM - 1) / GBM;
-        n_tile = tile / mt;
-        m_tile = tile - n_tile * mt;
-    }
-    const int m0 = m_tile * GBM, n0 = n_tile * GG_BN;
-    const int nk = p.K / DBK;
-
-    const char* src[SH::PT];
-#pragma unroll
-    for (int q = 0; q < SH::PT; ++q) {
-        const int row = 8 * (wave + 8 * q) + (lane >> 3);
-        const int c = (lane & 7) ^ ((row >> 1) & 7);
-        int64_t grow;
-        const __bf16* base;
-        if (row < GBM) {
-            base = (const __bf16*)p.a;
-            grow = (int64_t)min(m0 + row, p.M - 1) * p.lda;
-        } else {
-            base = p.w;
-            const int r = row - GBM;
-            grow = (int64_t)(r < GG_BN ? n0 + r : p.F + n0 + (r - GG_BN)) * p.K;
-        }
-        src[q] = (const char*)(base + grow + 8 * c);
-    }
-    auto issue = [&](int kt, int stage) {
-        char* st = lds + stage * SH::STAGE;
-        const int koff = kt * DBK * 2;
-#pragma unroll
-        for (int q = 0; q < SH::PT; ++q)
-            __builtin_amdgcn_global_load_lds((gvoid)(src[q] + koff), (lvoid)(st + (wave + 8 * q) * 1024), 16, 0, 0);
-    };
-
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-    // Row offsets (chunk added per k-step): X blocks j, value and gate blocks fb.
-    uint32_t xrow[2], vrow[5], grow_[5];
-    int xsw[2], vsw[5], gsw[5];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int r = 32 * tb + 16 * j + (lane & 15);
-        xrow[j] = r * 128;
-        xsw[j] = (r >> 1) & 7;
-    }
-#pragma unroll
-    for (int fb = 0; fb < 5; ++fb) {
-        const int rv = GBM + 80 * vg + 16 * fb + (lane & 15);
-        const int rg = rv + GG_BN;
-        vrow[fb] = rv * 128;
-        vsw[fb] = (rv >> 1) & 7;
-        grow_[fb] = rg * 128;
-        gsw[fb] = (rg >> 1) & 7;
-    }
-    f32x4 accv[2][5], accg[2][5];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int fb = 0; fb < 5; ++fb) accv[j][fb] = accg[j][fb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // The MFMAs of k-step ks of the stage at sb.
-    auto kstep = [&](uint32_t sb, int ks) {
-        const int chunk = 4 * ks + (lane >> 4);
-        u32x4 x[2], v[5], g[5];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) x[j] = lds_b128<0>(sb + xrow[j] + ((chunk ^ xsw[j]) << 4));
-#pragma unroll
-        for (int fb = 0; fb < 5; ++fb) {
-            v[fb] = lds_b128<0>(sb + vrow[fb] + ((chunk ^ vsw[fb]) << 4));
-            g[fb] = lds_b128<0>(sb + grow_[fb] + ((chunk ^ gsw[fb]) << 4));
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(x[0]), "+v"(x[1]), "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]),
-                       "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]));
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int fb = 0; fb < 5; ++fb) {
-                accv[j][fb] = mfma16x16x32(__builtin_bit_cast(bf16x8, v[fb]), __builtin_bit_cast(bf16x8, x[j]),
-                                           accv[j][fb]);
-                accg[j][fb] = mfma16x16x32(__builtin_bit_cast(bf16x8, g[fb]), __builtin_bit_cast(bf16x8, x[j]),
-                                           accg[j][fb]);
-            }
-    };
-
-#pragma unroll
-    for (int st = 0; st < SH::NS - 1; ++st)
-        if (st < nk) issue(st, st);
-    for (int kt = 0; kt < nk; ++kt) {
-        wait_tiles_after<SH::PT, SH::NS - 2>(min(nk - 1 - kt, SH::NS - 2));
-        __builtin_amdgcn_s_barrier();  // everyone's pieces of tile kt landed; the stage of tile kt-1 is free
-        if (kt + SH::NS - 1 < nk) issue(kt + SH::NS - 1, (kt + SH::NS - 1) % SH::NS);
-        const uint32_t sb = lds0 + (kt % SH::NS) * SH::STAGE;
-        if constexpr (SH::KSPLIT) {
-            kstep(sb, kg);
-        } else {
-            kstep(sb, 0);
-            kstep(sb, 1);
-        }
-    }
-
-    // BM = 64: wavefront (tb, vg, 1) hands its sums to (tb, vg, 0), which
-    // finishes the outputs.
-    if constexpr (SH::KSPLIT) {
-        __syncthreads();  // every wavefront is past its last LDS operand read
-        float* red = (float*)lds + ((tb * 2 + vg) * 20) * 64 * 4;  // 20 f32x4 per lane
-        if (kg == 1) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int fb = 0; fb < 5; ++fb) {
-                    *(f32x4*)(red + ((j * 5 + fb) * 64 + lane) * 4) = accv[j][fb];
-                    *(f32x4*)(red + ((10 + j * 5 + fb) * 64 + lane) * 4) = accg[j][fb];
-                }
-        }
-        __syncthreads();
-        if (kg == 1) return;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int fb = 0; fb < 5; ++fb) {
-                accv[j][fb] += *(const f32x4*)(red + ((j * 5 + fb) * 64 + lane) * 4);
-                accg[j][fb] += *(const f32x4*)(red + ((10 + j * 5 + fb) * 64 + lane) * 4);
-            }
-    }
-
-    // Epilogue: token m0 + 32 tb + 16 j + lane % 16, outputs n0 + 80 vg + 16 fb
-    // + 4 (lane / 16) + 0..3: (value + bias) * GELU(gate + gate bias).
-#pragma unroll
-    for (int fb = 0; fb < 5; ++fb) {
-        const int n = n0 + 80 * vg + 16 * fb + 4 * (lane >> 4);
-        float bv[4] = {0.f, 0.f, 0.f, 0.f}, bg[4] = {0.f, 0.f, 0.f, 0.f};
-        if (p.bias != nullptr) {
-            const bf16x4 b1 = *(const bf16x4*)(p.bias + n);
-            const bf16x4 b2 = *(const bf16x4*)(p.bias + p.F + n);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                bv[e] = bf16_to_f32(b1[e]);
-                bg[e] = bf16_to_f32(b2[e]);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int m = m0 + 32 * tb + 16 * j + (lane & 15);
-            if (m >= p.M) continue;
-            float o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (accv[j][fb][e] + bv[e]) * gelu_erf(accg[j][fb][e] + bg[e]);
-            if (p.out_f32) {
-                *(f32x4*)((float*)p.out[0] + (int64_t)m * p.ldo + n) = f32x4{o[0], o[1], o[2], o[3]};
-            } else {
-                const bf16x4 ob = {f32_to_bf16(o[0]), f32_to_bf16(o[1]), f32_to_bf16(o[2]), f32_to_bf16(o[3])};
-                *(bf16x4*)((bf16*)p.out[0] + (int64_t)m * p.ldo + n) = ob;
-            }
-        }
-    }
-}
-
-template <int BM, int BN, int NS, bool GEGLU>
-hipError_t launch_dma(const GemmParams& p, hipStream_t s) {
-    const int bn_out = GEGLU ? BN / 2 : BN;
-    dim3 grid((p.M + BM - 1) / BM, p.N / bn_out);
+// The 64 x 64 kernel at three stages.
+hipError_t launch_dma64(const GemmParams& p, hipStream_t s) {
+    dim3 grid((p.M + 63) / 64, p.N / 64);
     if (p.tpx > 0) grid = dim3((unsigned)(p.n_xcd * p.tpx * p.splitk), 1);
-    if constexpr (!GEGLU && BM == 64 && BN == 64) {
-        if (p.a_mode == 1) {
-            gemm_dma_kernel<BM, BN, NS, false, false, 1><<<grid, 256, 0, s>>>(p);
-            return hipGetLastError();
-        }
-        if (p.a_mode == 2) {
-            gemm_dma_kernel<BM, BN, NS, false, false, 2><<<grid, 256, 0, s>>>(p);
-            return hipGetLastError();
-        }
-    }
-    if (!GEGLU && p.conv_W > 0)
-        gemm_dma_kernel<BM, BN, NS, GEGLU, true, 0><<<grid, 256, 0, s>>>(p);
+    if (p.a_mode == 1)
+        gemm_dma_kernel<64, 64, 3, false, 1><<<grid, 256, 0, s>>>(p);
+    else if (p.a_mode == 2)
+        gemm_dma_kernel<64, 64, 3, false, 2><<<grid, 256, 0, s>>>(p);
+    else if (p.conv_W > 0)
+        gemm_dma_kernel<64, 64, 3, true, 0><<<grid, 256, 0, s>>>(p);
     else
-        gemm_dma_kernel<BM, BN, NS, GEGLU, false, 0><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<64, 64, 3, false, 0><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -1264,36 +1027,10 @@ bool gemm_shape_ok(const GemmParams& p) {
 
 namespace {
 
-// Split of a convolution GEMM over 128 x 128 tiles: as many pieces per tile
-// as still fit one workgroup per compute unit, each at least 16 k-tiles
-// long, used only when the split launch fills at least 90% of the compute
-// units (else the unsplit 64 x 64 tiles, two workgroups per compute unit,
-// are faster).
 struct SplitPlan {
     int splitk, n_xcd, tpx, n_tiles;
     size_t bytes;
 };
-
-SplitPlan split_plan(int M, int N, int K, const DeviceLayout& d) {
-    SplitPlan sp{1, 1, 0, 0, 0};
-    const int cus = d.cus;
-    if (!d.xcd_merge || N % 128 != 0 || K % DBK != 0) return sp;
-    const int64_t tiles = (int64_t)((M + 127) / 128) * (N / 128);
-    if (tiles < 1 || tiles > GEMM_SPLIT_COUNTERS) return sp;
-    const int n_xcd = d.n_xcd;
-    const int64_t tpx = (tiles + n_xcd - 1) / n_xcd;
-    int64_t k = cus / (n_xcd * tpx);
-    const int64_t k_max = (K / DBK) / 16;
-    if (k > k_max) k = k_max;
-    if (k > 8) k = 8;
-    if (k < 2 || 10 * n_xcd * tpx * k < 9 * (int64_t)cus) return sp;
-    sp.splitk = (int)k;
-    sp.n_xcd = n_xcd;
-    sp.tpx = (int)tpx;
-    sp.n_tiles = (int)tiles;
-    sp.bytes = (size_t)GEMM_SPLIT_COUNTERS * 4 + (size_t)n_xcd * tpx * k * 128 * 128 * 4;
-    return sp;
-}
 
 // Split of a plain GEMM over 64 x 64 tiles when they are fewer than the
 // compute units (one workgroup per compute unit and the rest idle): about
@@ -1334,17 +1071,19 @@ SplitPlan split_plan_plain(int M, int N, int K, const DeviceLayout& d) {
 // only ever needs less).
 size_t gemm_split_ws_bytes(int M, int N, int K, bool conv) {
     const DeviceLayout d = device_layout_unmasked();
-    return conv ? split_plan(M, N, K, d).bytes : split_plan_plain(M, N, K, d).bytes;
+    const size_t narrow = conv ? 0 : split_plan_plain(M, N, K, d).bytes;
+    const size_t wide = wide_split_bytes(M, N, K, d);
+    return wide > narrow ? wide : narrow;
 }
 
 namespace {
 
 // The kernel a product runs on.
-enum GemmKind { GK_DMA_128, GK_DMA_64, GK_G80, GK_DMA_GEGLU, GK_GEGLU160, GK_GEGLU160_64, GK_REG_22, GK_REG_12, GK_REG_11 };
+enum GemmKind { GK_DMA_64, GK_G80, GK_REG_22, GK_REG_12, GK_REG_11, GK_WIDE };
 
-// Validates p, picks its kernel, and sets the fields of a split or
-// XCD-ordered launch.
-hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind) {
+// Validates p, picks its kernel among those of this file, and sets the
+// fields of a split or XCD-ordered launch.
+hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
     if (p.conv_W > 0 && !gemm_shape_ok(p)) return hipErrorInvalidValue;
     if (p.a_mode == 2) {  // cross-attention epilogue: the 64 x 64 pipelined kernel, unsplit
         if (p.a_f32 || p.geglu || p.conv_W > 0 || p.K % DBK != 0 || p.N % 64 != 0 || p.seg < p.N || p.out_f32 ||
@@ -1370,37 +1109,22 @@ hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind) {
     }
     p.splitk = 1;
     p.tpx = 0;
-    const DeviceLayout dl = device_layout(s);
-    if (p.conv_W > 0 && p.split_ws != nullptr) {
-        const SplitPlan sp = split_plan(p.M, p.N, p.K, dl);
-        if (sp.splitk > 1 && p.split_ws_bytes >= sp.bytes && ((uintptr_t)p.split_ws & 15u) == 0) {
-            p.splitk = sp.splitk;
-            p.n_xcd = sp.n_xcd;
-            p.tpx = sp.tpx;
-            p.n_tiles = sp.n_tiles;
-            kind = GK_DMA_128;
-            return hipSuccess;
-        }
-    }
     // Unsplit launches: when W (rows x K) is at least four times X (M x K),
     // each XCD takes a contiguous n-major range of tiles, so a W tile is
     // fetched into one XCD's L2 (the hardware deals workgroups round-robin
     // over the XCDs, which with few token tiles sends every W tile to all of
-    // them).  At 512 tokens (2048 px level 2): GEGLU (10240 W rows) 37.4 ->
-    // 25.5 us, Q/K/V (3840) 16.4 -> 13.6 us; at ratios of 1 to 2.5 it
-    // changed nothing measurable.
-    auto map_xcd = [&](int bm, int bn_out) {
-        const int64_t w_rows = p.geglu ? 2 * (int64_t)p.N : p.N;
-        if (!dl.xcd_merge || w_rows < 4 * (int64_t)p.M) return;
-        const int64_t tiles = (int64_t)((p.M + bm - 1) / bm) * (p.N / bn_out);
+    // them).  At 512 tokens (2048 px level 2): Q/K/V (3840 W rows) 16.4 ->
+    // 13.6 us; at ratios of 1 to 2.5 it changed nothing measurable.
+    auto map_xcd = [&]() {
+        if (!dl.xcd_merge || p.N < 4 * (int64_t)p.M) return;
+        const int64_t tiles = (int64_t)((p.M + 63) / 64) * (p.N / 64);
         const int n_xcd = dl.n_xcd;
         if (tiles < n_xcd || tiles > INT32_MAX / 2) return;
         p.n_xcd = n_xcd;
         p.tpx = (int)((tiles + n_xcd - 1) / n_xcd);
         p.n_tiles = (int)tiles;
     };
-    // bf16 X with K % 64 == 0: the pipelined kernel, with the largest tile
-    // that still gives about a workgroup per compute unit.
+    // bf16 X with K % 64 == 0: the pipelined kernels.
     if (!p.a_f32 && p.K % DBK == 0 && p.seg % 4 == 0) {
         if (!p.geglu && p.conv_W == 0 && p.split_ws != nullptr && p.N % 64 == 0 && p.a_mode != 2) {
             const SplitPlan sp = split_plan_plain(p.M, p.N, p.K, dl);
@@ -1413,41 +1137,9 @@ hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind) {
                 return hipSuccess;
             }
         }
-        if (p.geglu) {
-            // 128 (else 64) tokens x 160 outputs when those tiles fit one per
-            // compute unit and fill at least three quarters of them (the
-            // block's 2048 x 2560 product, the level-2 512 x 5120 one: 256
-            // tiles); the 64-token tiles run XCD-contiguous when W has four
-            // times X's rows.
-            const bool gg_form = p.N % 160 == 0 && p.resid == nullptr && p.out_bf16 == nullptr &&
-                                 p.bias2 == nullptr && p.seg >= p.N && p.w_seg_rows == 0 && p.seg_stride == 0;
-            const int64_t t128 = gg_form ? (int64_t)((p.M + 127) / 128) * (p.N / 160) : 0;
-            const int64_t t64 = gg_form ? (int64_t)((p.M + 63) / 64) * (p.N / 160) : 0;
-            const bool wide_w = 2 * (int64_t)p.N >= 4 * (int64_t)p.M;
-            auto fits = [&](int64_t t) { return t > 0 && t <= dl.cus && 4 * t >= 3 * (int64_t)dl.cus; };
-            const int64_t tg = fits(t128) ? t128 : (fits(t64) ? t64 : 0);
-            if (tg > 0) {
-                if (wide_w && dl.xcd_merge && tg >= dl.n_xcd) {
-                    p.n_xcd = dl.n_xcd;
-                    p.tpx = (int)((tg + dl.n_xcd - 1) / dl.n_xcd);
-                    p.n_tiles = (int)tg;
-                }
-                kind = tg == t128 ? GK_GEGLU160 : GK_GEGLU160_64;
-                return hipSuccess;
-            }
-            // value/gate pairs on 64-token tiles at two stages (48 KB of LDS: three
-            // workgroups per compute unit): 25.3 us against 28.7 for 128-token
-            // tiles and 35.2 for three stages at the 2048 x 2 x 2560 x 640 shape
-            if (p.N % 64 == 0) {
-                map_xcd(64, 64);
-                kind = GK_DMA_GEGLU;
-                return hipSuccess;
-            }
-        } else {
-            // 128x128 tiles only with at least two per compute unit; else 64x64
-            // tiles at three stages (48 KB of LDS: three workgroups per compute
-            // unit), measured faster at M = 2048 for every N from 640 to 1920.
-            // Balanced 64 x 80 tiles when the 64 x 64 ones would divide
+        if (!p.geglu) {
+            // 64x64 tiles at three stages (48 KB of LDS: three workgroups per
+            // compute unit).  Balanced 64 x 80 tiles when the 64 x 64 ones would divide
             // unevenly over the compute units while the 80-row tiles come to
             // at most three per compute unit and fill at least three quarters
             // of them: a 2048 x 640 product is 256 tiles instead of 320, the
@@ -1462,14 +1154,8 @@ hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind) {
                 kind = GK_G80;
                 return hipSuccess;
             }
-            const int64_t mt128 = (p.M + 127) / 128;
-            if (p.a_mode == 0 && p.N % 128 == 0 && mt128 * (p.N / 128) >= 2 * (int64_t)dl.cus) {
-                map_xcd(128, 128);
-                kind = GK_DMA_128;
-                return hipSuccess;
-            }
             if (p.N % 64 == 0) {
-                map_xcd(64, 64);
+                map_xcd();
                 kind = GK_DMA_64;
                 return hipSuccess;
             }
@@ -1489,10 +1175,42 @@ hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind) {
     return hipSuccess;
 }
 
-hipError_t launch_planned(const GemmParams& p, GemmKind kind, hipStream_t s) {
+// Microseconds that a planned launch of this file takes, from the measured
+// times per k-tile (64 of K) of its tiles: a 64 x 64 tile is bound by its
+// compute unit's share of the L2 (0.30 us a k-tile, however many share the
+// unit), a 64 x 80 tile 0.32 us alone on its unit and 0.26 shared;
+// a launch's ends 5 to 7, a merge of split pieces 3.
+double narrow_us(const GemmParams& p, GemmKind kind, int cus) {
+    const double nk = (double)(p.K / DBK) / p.splitk;
+    auto tiles = [&](int bm, int bn) { return (double)((p.M + bm - 1) / bm) * (p.N / bn) * p.splitk; };
+    auto shared = [&](double t) { return t > cus ? t / cus : 1.0; };
+    const double merge = p.splitk > 1 ? 3.0 : 0.0;
     switch (kind) {
-        case GK_DMA_128: return launch_dma<128, 128, 3, false>(p, s);
-        case GK_DMA_64: return launch_dma<64, 64, 3, false>(p, s);
+        case GK_DMA_64: return 5.8 + merge + shared(tiles(64, 64)) * nk * 0.30;
+        case GK_G80: return 7.0 + ceil(tiles(64, 80) / cus) * nk * (tiles(64, 80) > cus ? 0.26 : 0.32);
+        default: return 1e9;
+    }
+}
+
+// The narrow kernels' plan, or the wide tiles' where they are estimated to
+// be faster (gemm_wide.hip); shape: the wide tile.
+hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind, int& shape) {
+    const DeviceLayout dl = device_layout(s);
+    const GemmParams in = p;
+    const hipError_t e = plan_narrow(p, dl, kind);
+    if (e != hipSuccess) return e;
+    GemmParams w = in;
+    if (plan_wide(w, dl, 0.97 * narrow_us(p, kind, dl.cus), shape)) {
+        p = w;
+        kind = GK_WIDE;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_planned(const GemmParams& p, GemmKind kind, int shape, hipStream_t s) {
+    switch (kind) {
+        case GK_WIDE: return launch_gemm_wide(p, shape, s);
+        case GK_DMA_64: return launch_dma64(p, s);
         case GK_G80: {
             // two stages (36 KB of LDS) when the tiles need several per compute unit
             const dim3 grid((unsigned)((p.M + G80_BM - 1) / G80_BM), (unsigned)(p.N / G80_BN));
@@ -1500,18 +1218,6 @@ hipError_t launch_planned(const GemmParams& p, GemmKind kind, hipStream_t s) {
                 gemm80_kernel<2><<<grid, 512, 0, s>>>(p);
             else
                 gemm80_kernel<4><<<grid, 512, 0, s>>>(p);
-            return hipGetLastError();
-        }
-        case GK_DMA_GEGLU: return launch_dma<64, 128, 2, true>(p, s);
-        case GK_GEGLU160:
-        case GK_GEGLU160_64: {
-            const int bm = kind == GK_GEGLU160 ? 128 : 64;
-            const dim3 grid = p.tpx > 0 ? dim3((unsigned)(p.n_xcd * p.tpx), 1)
-                                        : dim3((unsigned)((p.M + bm - 1) / bm), (unsigned)(p.N / GG_BN));
-            if (kind == GK_GEGLU160)
-                geglu160_kernel<128><<<grid, 512, 0, s>>>(p);
-            else
-                geglu160_kernel<64><<<grid, 512, 0, s>>>(p);
             return hipGetLastError();
         }
         case GK_REG_22: return launch_shape<2, 2>(p, s);
@@ -1536,16 +1242,18 @@ void dma64_grid(const GemmParams& p, int& gx, int& gy) {
 hipError_t launch_gemm(const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
     GemmKind kind;
-    const hipError_t e = plan_gemm(p, s, kind);
-    return e != hipSuccess ? e : launch_planned(p, kind, s);
+    int shape = 0;
+    const hipError_t e = plan_gemm(p, s, kind, shape);
+    return e != hipSuccess ? e : launch_planned(p, kind, shape, s);
 }
 
 hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipStream_t s) {
     GemmParams a = a_in, b = b_in;
     GemmKind ka, kb;
-    hipError_t e = plan_gemm(a, s, ka);
+    int sa = 0, sb = 0;
+    hipError_t e = plan_gemm(a, s, ka, sa);
     if (e != hipSuccess) return e;
-    e = plan_gemm(b, s, kb);
+    e = plan_gemm(b, s, kb, sb);
     if (e != hipSuccess) return e;
     // One launch when both run on the 64 x 64 pipelined kernel and at most
     // one of them splits K (the split region holds one product's partials);
@@ -1571,8 +1279,8 @@ hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipS
             gemm_dma_pair_kernel<64, 64, 3, 0><<<dim3((unsigned)total), 256, 0, s>>>(pp);
         return hipGetLastError();
     }
-    e = launch_planned(a, ka, s);
-    return e != hipSuccess ? e : launch_planned(b, kb, s);
+    e = launch_planned(a, ka, sa, s);
+    return e != hipSuccess ? e : launch_planned(b, kb, sb, s);
 }
 
 }  // namespace pcpp
