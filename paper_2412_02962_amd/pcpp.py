@@ -211,6 +211,10 @@ def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
     import torch  # device memory and streams only
+    if torch.cuda.is_initialized():
+        # the current stream's handle without a Stream object around it: 0.3
+        # us a call instead of 2.9 (a call of the library takes 4 to 8)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return torch.cuda.current_stream().cuda_stream
 
 
