@@ -298,32 +298,11 @@ int run_module(const pcpp_geom_t* g, const ModuleW& mw, const pcpp_basic_block_w
         gp.zero2 = (int*)attn_ws;
         gp.n_zero2 = n1 > n2 ? n1 : n2;
     }
-    // proj_in, and beside it in the same launch the first chunk's text K/V
-    // (independent of the band).  When the band's tokens fill whole 64-token
-    // tiles, proj_in applies the GroupNorm itself while staging x (from the
-    // statistics launch's records), else a separate apply writes it to t16.
+    // proj_in, and beside it (in the same launch where that is faster) the
+    // first chunk's text K/V, independent of the band.
+    PCPP_CHECK(launch_group_norm(gp, s));
     {
-        const bool gn_in_gemm = N % 64 == 0 && C % 64 == 0 && C <= GEMM_GN_MAXC;
-        GemmParams pin = gemm(t16, C, false, mw.proj_in_w, mw.proj_in_b, rows, C, C, hid, C, true);
-        if (gn_in_gemm) {
-            PCPP_CHECK(launch_group_norm_stats(gp, s));
-            pin.a = x;
-            pin.a_mode = 1;
-            pin.gn.stats = gp.stats;
-            pin.gn.chunks = gp.chunks;
-            pin.gn.G = gp.G;
-            pin.gn.B = gp.B;
-            pin.gn.eps = gp.eps;
-            pin.gn.bands = gp.bands;
-            pin.gn.n_bands = gp.n_bands;
-            pin.gn.band = gp.band;
-            pin.gn.own_out = gp.own_out;
-            pin.gn_gamma = gp.gamma;
-            pin.gn_beta = gp.beta;
-            pin.gn_N = N;
-        } else {
-            PCPP_CHECK(launch_group_norm(gp, s));
-        }
+        const GemmParams pin = gemm(t16, C, false, mw.proj_in_w, mw.proj_in_b, rows, C, C, hid, C, true);
         PCPP_CHECK(L.kv_grouped && depth > 0 ? gemm_pair_s(pin, text_kv(0)) : gemm_s(pin));
     }
 
@@ -390,7 +369,6 @@ int run_module(const pcpp_geom_t* g, const ModuleW& mw, const pcpp_basic_block_w
         // attention itself (one head per tile), else it runs separately.
         if (T <= GEMM_XA_MAXT && N % 64 == 0) {
             GemmParams xq = gemm(t16, C, false, w.attn2_q_w, nullptr, rows, C, C, a16, C, false);
-            xq.a_mode = 2;
             xq.xa_k = k2;
             xq.xa_v = v2;
             xq.xa_T = T;

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "gn_merge.h"
 #include "kernels.h"
 
 namespace pcpp {
@@ -56,20 +55,7 @@ struct GemmParams {
     // > 0: output segment s at out[0] + s * seg_stride elements (out[1..2]
     // unused), for any number of segments.
     int64_t seg_stride = 0;
-    // a_mode 1: GroupNorm of X applied while X is staged (bf16 X; K = C <=
-    // GEMM_GN_MAXC channels, G <= 256 groups; gn_N tokens per image, a
-    // multiple of 64): channel k of token m becomes X * sc + sh with the
-    // scale and shift of m's image, from the statistics launch's records in
-    // gn (and the other bands' for the synchronized form), in the arithmetic
-    // of the GroupNorm apply kernel (the same bits).  Runs on the 64 x 64
-    // pipelined kernel; the workgroup holding image b's first token tile and
-    // the first W tile writes the band's own statistics to gn.own_out.
-    int32_t a_mode = 0;
-    GnStatsSrc gn = {};
-    const __bf16* gn_gamma = nullptr;
-    const __bf16* gn_beta = nullptr;
-    int32_t gn_N = 0;
-    // a_mode 2: cross-attention in the epilogue (bf16 X and output, N = heads
+    // xa_T > 0: cross-attention in the epilogue (bf16 X and output, N = heads
     // x 64, xa_N tokens per image, a multiple of 64; no bias, residual or
     // copy): the product is the attention's Q, and the workgroup of token
     // tile m and head h goes on to softmax(Q K_h^T / 8) V_h over the xa_T <=
@@ -83,7 +69,6 @@ struct GemmParams {
     int32_t splitk = 1, n_xcd = 1, tpx = 0, n_tiles = 0;
     int32_t m_major = 0;  // wide tiles: all W tiles of one token tile together
 };
-constexpr int GEMM_GN_MAXC = 1280;
 constexpr int GEMM_XA_MAXT = 96;  // keys of the cross-attention epilogue
 
 // Bytes of split-K workspace a GEMM of this shape can use (0: it runs
@@ -97,7 +82,7 @@ size_t gemm_split_ws_bytes(int M, int N, int K, bool conv = true);
 // that are estimated fastest for p, sets p's launch fields and `shape`, and
 // returns true if the estimate lies under limit_us; wide_split_bytes: the
 // most workspace such a plan of a product of these sizes can use.
-bool plan_wide(GemmParams& p, const DeviceLayout& dl, double limit_us, int& shape);
+bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& us, int& shape);
 size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl);
 hipError_t launch_gemm_wide(const GemmParams& p, int shape, hipStream_t s);
 
@@ -146,9 +131,6 @@ size_t group_norm_ws_bytes(int B, int G, int N);
 bool norm_shapes_ok(int C, int G);  // GroupNorm and LayerNorm: C <= 2048
 bool gn_shapes_ok(int C, int G);    // GroupNorm alone: C <= 2560
 hipError_t launch_group_norm(GroupNormParams p, hipStream_t s);
-// The statistics launch alone (sets p.chunks): for a GEMM that applies the
-// GroupNorm while staging its operand (GemmParams::a_mode).
-hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s);
 
 // LayerNorm over the channel axis of fp32 rows, bf16 output.
 struct LayerNormParams {

@@ -258,27 +258,16 @@ __device__ __forceinline__ void wait_tiles_after(int later) {
     }
 }
 
-// LDS floats of the GroupNorm table of a_mode 1: scale and shift per
-// channel (the merge's 256 x 3 scratch shares their space), then the group
-// means and reciprocal deviations.
-constexpr int GN_TAB_FLOATS = 2 * GEMM_GN_MAXC + 2 * 256;
 // LDS floats of the cross-attention epilogue's K rows and transposed V.
 constexpr int XA_TAB_FLOATS = (GEMM_XA_MAXT * 128 + 64 * 200) / 4;
-static_assert(2 * GEMM_GN_MAXC >= 3 * 256, "the merge scratch fits the scale and shift tables");
 
 // One workgroup's tile of the product; (bx, by) is its place in the
 // product's own grid (blockIdx of a single launch); lds holds NS stages,
-// gn_tab GN_TAB_FLOATS floats when AMODE is 1.
-//
-// AMODE 1 applies GroupNorm to X in its LDS stage: after the products of
-// k-tile kt every lane rewrites the pieces of k-tile kt + 1 its own direct
-// loads brought, published by the next barrier.
-template <int BM, int BN, int NS, bool CONV, int AMODE>
+// xa_tab XA_TAB_FLOATS floats with XATT (the cross-attention epilogue).
+template <int BM, int BN, int NS, bool CONV, bool XATT>
 __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx, const int by, char* lds,
-                                              float* gn_tab) {
-    constexpr bool AGN = AMODE == 1;
-    constexpr bool XATT = AMODE == 2;
-    static_assert(!(AGN || XATT) || (BM == 64 && BN == 64 && !CONV), "plain 64 x 64 tiles only");
+                                              float* xa_tab) {
+    static_assert(!XATT || (BM == 64 && BN == 64 && !CONV), "plain 64 x 64 tiles only");
     constexpr int WMB = BM / 64;                      // 32-token blocks per wavefront
     constexpr int WNB = BN / 64;                      // 32-row W blocks per wavefront
     constexpr int XP = BM / 32;                       // 1 KB X pieces per wavefront per k-tile
@@ -456,12 +445,12 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
     };
 
-    // Cross-attention (AMODE 2).  gn_tab holds K_h as rows of 128 bytes (the
+    // Cross-attention.  xa_tab holds K_h as rows of 128 bytes (the
     // operand swizzle; keys past xa_T zero) and V_h transposed, a row of
     // 200 bytes per head dimension (keys along the row; 200 keeps the eight-
     // byte reads of 32 dimensions on distinct banks).
     constexpr int XA_VT_STRIDE = 200;
-    char* xa = (char*)gn_tab;
+    char* xa = (char*)xa_tab;
     char* xa_vt = xa + GEMM_XA_MAXT * 128;
     auto xatt_stage = [&]() {
         const int img = m0 / p.xa_N;
@@ -568,84 +557,16 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
     };
 
-    if constexpr (AGN) {
-        // X arrives with the direct loads like W; each lane then rewrites in
-        // place the 16-byte pieces its own loads brought (so its own wait
-        // suffices), with the GroupNorm applied, before the barrier that
-        // publishes the stage.  Piece i of the lane: row 8 (wave + 4 i) +
-        // lane / 8, source chunk (lane % 8) ^ ((row / 2) % 8).
-        float* sc = gn_tab;
-        float* sh = gn_tab + GEMM_GN_MAXC;
-        auto gn_rewrite = [&](int kt, int stage) {
 #pragma unroll
-            for (int i = 0; i < XP; ++i) {
-                const int r = 8 * (wave + 4 * i) + (lane >> 3);
-                const int c0 = kt * DBK + 8 * ((lane & 7) ^ ((r >> 1) & 7));
-                bf16x8* at = (bf16x8*)(lds + stage * STAGE + (wave + 4 * i) * 1024 + lane * 16);
-                const bf16x8 v = *at;
-                float a[8], b[8];
-                *(f32x4*)&a[0] = *(const f32x4*)(sc + c0);
-                *(f32x4*)&a[4] = *(const f32x4*)(sc + c0 + 4);
-                *(f32x4*)&b[0] = *(const f32x4*)(sh + c0);
-                *(f32x4*)&b[4] = *(const f32x4*)(sh + c0 + 4);
-                bf16x8 y;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) y[e] = f32_to_bf16(__builtin_fmaf((float)v[e], a[e], b[e]));
-                *at = y;
-            }
-        };
-        // The first two k-tiles in flight while the statistics are merged.
-        const int nkt = kt1 - kt0;
-        issue(kt0, 0);
-        if (nkt > 1) issue(kt0 + 1, 1);
-        {
-            const int img = m0 / p.gn_N;
-            float* g_mean = gn_tab + 2 * GEMM_GN_MAXC;
-            float* g_rstd = g_mean + 256;
-            gn_group_stats(p.gn, img, m0 == img * p.gn_N && n0 == 0 && piece == 0, gn_tab, g_mean, g_rstd);
-            const int cg = p.K / p.gn.G;
-            for (int c = tid; c < p.K; c += 256) {
-                const int g = c / cg;
-                const float a = g_rstd[g] * bf16_to_f32(p.gn_gamma[c]);
-                sc[c] = a;
-                sh[c] = bf16_to_f32(p.gn_beta[c]) - g_mean[g] * a;
-            }
-            __syncthreads();
-        }
-        // X(kt0) landed: after it W(kt0) and, if issued, k-tile kt0 + 1.
-        if (nkt > 1)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP + PT));
-        else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP));
-        gn_rewrite(kt0, 0);
-        for (int kt = kt0; kt < kt1; ++kt) {
-            const int i = kt - kt0;
-            wait_tiles_after<PT, NS - 2>(min(kt1 - 1 - kt, NS - 2));
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this lane's rewrite of X(kt)
-            __builtin_amdgcn_s_barrier();
-            if (kt + NS - 1 < kt1) issue(kt + NS - 1, (i + NS - 1) % NS);
-            mfma_tile(lds0 + (i % NS) * STAGE);
-            if (kt + 1 < kt1) {
-                // X(kt + 1) landed: after it W(kt + 1) and, if issued, k-tile kt + 2.
-                if (kt + 2 < kt1)
-                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP + PT));
-                else
-                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP));
-                gn_rewrite(kt + 1, (i + 1) % NS);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < NS - 1; ++s)
-            if (kt0 + s < kt1) issue(kt0 + s, s);
-        if constexpr (XATT) xatt_stage();  // its loads wait behind the first k-tiles'
-        for (int kt = kt0; kt < kt1; ++kt) {
-            // k-tiles issued after kt so far: min(kt1 - 1 - kt, NS - 2), PT loads each
-            wait_tiles_after<PT, NS - 2>(min(kt1 - 1 - kt, NS - 2));
-            __builtin_amdgcn_s_barrier();  // everyone's pieces of tile kt landed; the stage of tile kt-1 is free
-            if (kt + NS - 1 < kt1) issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
-            mfma_tile(lds0 + ((kt - kt0) % NS) * STAGE);
-        }
+    for (int s = 0; s < NS - 1; ++s)
+        if (kt0 + s < kt1) issue(kt0 + s, s);
+    if constexpr (XATT) xatt_stage();  // its loads wait behind the first k-tiles'
+    for (int kt = kt0; kt < kt1; ++kt) {
+        // k-tiles issued after kt so far: min(kt1 - 1 - kt, NS - 2), PT loads each
+        wait_tiles_after<PT, NS - 2>(min(kt1 - 1 - kt, NS - 2));
+        __builtin_amdgcn_s_barrier();  // everyone's pieces of tile kt landed; the stage of tile kt-1 is free
+        if (kt + NS - 1 < kt1) issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
+        mfma_tile(lds0 + ((kt - kt0) % NS) * STAGE);
     }
 
     if constexpr (XATT) {
@@ -787,11 +708,11 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     }
 }
 
-template <int BM, int BN, int NS, bool CONV, int AMODE>
+template <int BM, int BN, int NS, bool CONV, bool XATT>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
-    __shared__ __attribute__((aligned(16))) float gn_tab[AMODE == 1 ? GN_TAB_FLOATS : AMODE == 2 ? XA_TAB_FLOATS : 4];
-    gemm_dma_body<BM, BN, NS, CONV, AMODE>(p, blockIdx.x, blockIdx.y, lds, gn_tab);
+    __shared__ __attribute__((aligned(16))) float xa_tab[XATT ? XA_TAB_FLOATS : 4];
+    gemm_dma_body<BM, BN, NS, CONV, XATT>(p, blockIdx.x, blockIdx.y, lds, xa_tab);
 }
 
 // Two independent plain products in one launch (so that neither pays a
@@ -804,15 +725,14 @@ struct GemmPair {
     int32_t gx_a, n_a, gx_b, b0;
 };
 
-template <int BM, int BN, int NS, int AMODE_A>
+template <int BM, int BN, int NS>
 __global__ __launch_bounds__(256) void gemm_dma_pair_kernel(GemmPair pp) {
     __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
-    __shared__ __attribute__((aligned(16))) float gn_tab[AMODE_A == 1 ? GN_TAB_FLOATS : 4];
     const int id = blockIdx.x;
     if (id < pp.n_a)
-        gemm_dma_body<BM, BN, NS, false, AMODE_A>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, gn_tab);
+        gemm_dma_body<BM, BN, NS, false, false>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, nullptr);
     else if (id >= pp.b0)
-        gemm_dma_body<BM, BN, NS, false, 0>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, gn_tab);
+        gemm_dma_body<BM, BN, NS, false, false>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -987,14 +907,12 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
 hipError_t launch_dma64(const GemmParams& p, hipStream_t s) {
     dim3 grid((p.M + 63) / 64, p.N / 64);
     if (p.tpx > 0) grid = dim3((unsigned)(p.n_xcd * p.tpx * p.splitk), 1);
-    if (p.a_mode == 1)
-        gemm_dma_kernel<64, 64, 3, false, 1><<<grid, 256, 0, s>>>(p);
-    else if (p.a_mode == 2)
-        gemm_dma_kernel<64, 64, 3, false, 2><<<grid, 256, 0, s>>>(p);
+    if (p.xa_T > 0)
+        gemm_dma_kernel<64, 64, 3, false, true><<<grid, 256, 0, s>>>(p);
     else if (p.conv_W > 0)
-        gemm_dma_kernel<64, 64, 3, true, 0><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<64, 64, 3, true, false><<<grid, 256, 0, s>>>(p);
     else
-        gemm_dma_kernel<64, 64, 3, false, 0><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<64, 64, 3, false, false><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -1085,18 +1003,12 @@ enum GemmKind { GK_DMA_64, GK_G80, GK_REG_22, GK_REG_12, GK_REG_11, GK_WIDE };
 // fields of a split or XCD-ordered launch.
 hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
     if (p.conv_W > 0 && !gemm_shape_ok(p)) return hipErrorInvalidValue;
-    if (p.a_mode == 2) {  // cross-attention epilogue: the 64 x 64 pipelined kernel, unsplit
+    if (p.xa_T != 0) {  // cross-attention epilogue: the 64 x 64 pipelined kernel, unsplit
         if (p.a_f32 || p.geglu || p.conv_W > 0 || p.K % DBK != 0 || p.N % 64 != 0 || p.seg < p.N || p.out_f32 ||
             p.resid != nullptr || p.out_bf16 != nullptr || p.bias != nullptr || p.bias2 != nullptr ||
             p.w_seg_rows != 0 || p.seg_stride != 0 || p.xa_k == nullptr || p.xa_v == nullptr || p.xa_T < 1 ||
             p.xa_T > GEMM_XA_MAXT || p.xa_N <= 0 || p.xa_N % 64 != 0 || p.M % p.xa_N != 0 || p.xa_ldkv < p.N ||
             p.xa_ldkv % 8 != 0)
-            return hipErrorInvalidValue;
-    } else if (p.a_mode != 0) {  // GroupNorm staging: the 64 x 64 pipelined kernel only
-        if (p.a_mode != 1 || p.a_f32 || p.geglu || p.conv_W > 0 || p.K % DBK != 0 || p.K > GEMM_GN_MAXC ||
-            p.N % 64 != 0 || p.seg % 4 != 0 || p.gn_N <= 0 || p.gn_N % 64 != 0 || p.M % p.gn_N != 0 || p.gn.G < 1 ||
-            p.gn.G > 256 || p.K % p.gn.G != 0 || p.gn.stats == nullptr || p.gn_gamma == nullptr ||
-            p.gn_beta == nullptr)
             return hipErrorInvalidValue;
     }
     if (p.w_seg_rows != 0 || p.seg_stride != 0) {  // the pipelined kernel's plain form only
@@ -1126,7 +1038,7 @@ hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
     };
     // bf16 X with K % 64 == 0: the pipelined kernels.
     if (!p.a_f32 && p.K % DBK == 0 && p.seg % 4 == 0) {
-        if (!p.geglu && p.conv_W == 0 && p.split_ws != nullptr && p.N % 64 == 0 && p.a_mode != 2) {
+        if (!p.geglu && p.conv_W == 0 && p.split_ws != nullptr && p.N % 64 == 0 && p.xa_T == 0) {
             const SplitPlan sp = split_plan_plain(p.M, p.N, p.K, dl);
             if (sp.splitk > 1 && p.split_ws_bytes >= sp.bytes && ((uintptr_t)p.split_ws & 15u) == 0) {
                 p.splitk = sp.splitk;
@@ -1147,7 +1059,7 @@ hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
             // four times X's rows: those keep the XCD-contiguous 64 x 64 tiles.
             const int64_t mt64 = (p.M + 63) / 64;
             const int64_t t80 = p.N % 80 == 0 ? mt64 * (p.N / 80) : 0;
-            const bool g80_form = p.a_mode == 0 && p.conv_W == 0 && p.w_seg_rows == 0 && p.seg_stride == 0 &&
+            const bool g80_form = p.xa_T == 0 && p.conv_W == 0 && p.w_seg_rows == 0 && p.seg_stride == 0 &&
                                   p.bias2 == nullptr && (p.seg >= p.N || (p.seg % 80 == 0 && p.N / p.seg <= 3));
             if (g80_form && p.N < 4 * (int64_t)p.M && t80 > 0 && t80 <= 3 * dl.cus && 4 * t80 >= 3 * (int64_t)dl.cus &&
                 mt64 * (p.N / 64) > dl.cus) {
@@ -1193,23 +1105,32 @@ double narrow_us(const GemmParams& p, GemmKind kind, int cus) {
 }
 
 // The narrow kernels' plan, or the wide tiles' where they are estimated to
-// be faster (gemm_wide.hip); shape: the wide tile.
-hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmKind& kind, int& shape) {
+// be faster (gemm_wide.hip).
+struct GemmPlan {
+    GemmKind kind;
+    int shape;  // wide tile
+    double us;  // estimated
+};
+
+hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmPlan& pl) {
     const DeviceLayout dl = device_layout(s);
     const GemmParams in = p;
-    const hipError_t e = plan_narrow(p, dl, kind);
+    const hipError_t e = plan_narrow(p, dl, pl.kind);
     if (e != hipSuccess) return e;
+    pl.us = narrow_us(p, pl.kind, dl.cus);
     GemmParams w = in;
-    if (plan_wide(w, dl, 0.97 * narrow_us(p, kind, dl.cus), shape)) {
+    double wide_us = 0.97 * pl.us;
+    if (plan_wide(w, dl, wide_us, pl.shape)) {
         p = w;
-        kind = GK_WIDE;
+        pl.kind = GK_WIDE;
+        pl.us = wide_us;
     }
     return hipSuccess;
 }
 
-hipError_t launch_planned(const GemmParams& p, GemmKind kind, int shape, hipStream_t s) {
-    switch (kind) {
-        case GK_WIDE: return launch_gemm_wide(p, shape, s);
+hipError_t launch_planned(const GemmParams& p, const GemmPlan& pl, hipStream_t s) {
+    switch (pl.kind) {
+        case GK_WIDE: return launch_gemm_wide(p, pl.shape, s);
         case GK_DMA_64: return launch_dma64(p, s);
         case GK_G80: {
             // two stages (36 KB of LDS) when the tiles need several per compute unit
@@ -1241,46 +1162,59 @@ void dma64_grid(const GemmParams& p, int& gx, int& gy) {
 
 hipError_t launch_gemm(const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
-    GemmKind kind;
-    int shape = 0;
-    const hipError_t e = plan_gemm(p, s, kind, shape);
-    return e != hipSuccess ? e : launch_planned(p, kind, shape, s);
+    GemmPlan pl;
+    const hipError_t e = plan_gemm(p, s, pl);
+    return e != hipSuccess ? e : launch_planned(p, pl, s);
 }
 
 hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipStream_t s) {
     GemmParams a = a_in, b = b_in;
-    GemmKind ka, kb;
-    int sa = 0, sb = 0;
-    hipError_t e = plan_gemm(a, s, ka, sa);
+    GemmPlan pa, pb;
+    hipError_t e = plan_gemm(a, s, pa);
     if (e != hipSuccess) return e;
-    e = plan_gemm(b, s, kb, sb);
+    e = plan_gemm(b, s, pb);
     if (e != hipSuccess) return e;
-    // One launch when both run on the 64 x 64 pipelined kernel and at most
-    // one of them splits K (the split region holds one product's partials);
-    // only the first may stage its X with GroupNorm, and neither carries the
-    // cross-attention epilogue.
-    if (ka == GK_DMA_64 && kb == GK_DMA_64 && a.conv_W == 0 && b.conv_W == 0 && !(a.splitk > 1 && b.splitk > 1) &&
-        a.a_mode <= 1 && b.a_mode == 0) {
-        GemmPair pp;
-        pp.a = a;
-        pp.b = b;
-        int gy_a, gy_b;
-        dma64_grid(a, pp.gx_a, gy_a);
-        dma64_grid(b, pp.gx_b, gy_b);
-        pp.n_a = pp.gx_a * gy_a;
-        const DeviceLayout dl = device_layout(s);
-        const int n_xcd = dl.n_xcd > 0 ? dl.n_xcd : 1;
-        pp.b0 = (pp.n_a + n_xcd - 1) / n_xcd * n_xcd;
-        const int64_t total = (int64_t)pp.b0 + (int64_t)pp.gx_b * gy_b;
-        if (total > INT32_MAX) return hipErrorInvalidValue;
-        if (a.a_mode == 1)
-            gemm_dma_pair_kernel<64, 64, 3, 1><<<dim3((unsigned)total), 256, 0, s>>>(pp);
-        else
-            gemm_dma_pair_kernel<64, 64, 3, 0><<<dim3((unsigned)total), 256, 0, s>>>(pp);
-        return hipGetLastError();
+    // One launch on the 64 x 64 pipelined kernel where that is estimated to
+    // be faster than the two planned ones: its workgroups share the compute
+    // units and it has one launch's ends (proj_in of the 2048 x 640 band and
+    // the two blocks' text K/V: 11 us against 8 + 10).  Neither carries the
+    // cross-attention epilogue, and at most one splits K (the split region
+    // holds one product's partials).
+    const DeviceLayout dl = device_layout(s);
+    GemmParams a64 = a;
+    const bool plain_a = !a.a_f32 && !a.geglu && a.conv_W == 0 && a.K % DBK == 0 && a.N % 64 == 0 && a.seg % 4 == 0 &&
+                         a.xa_T == 0;
+    if (pa.kind != GK_DMA_64 && plain_a) {
+        a64 = a_in;
+        a64.splitk = 1;
+        a64.tpx = 0;
     }
-    e = launch_planned(a, ka, sa, s);
-    return e != hipSuccess ? e : launch_planned(b, kb, sb, s);
+    if (pb.kind == GK_DMA_64 && b.conv_W == 0 && b.xa_T == 0 && plain_a && !(a64.splitk > 1 && b.splitk > 1)) {
+        auto work = [](const GemmParams& p) {
+            return (double)((p.M + 63) / 64) * (p.N / 64) * (p.K / DBK);
+        };
+        const double wgs = (work(a64) / (a64.K / DBK)) * a64.splitk + (work(b) / (b.K / DBK)) * b.splitk;
+        const double longest = fmax((double)(a64.K / DBK) / a64.splitk, (double)(b.K / DBK) / b.splitk);
+        const double us = 5.8 + (a64.splitk > 1 || b.splitk > 1 ? 3.0 : 0.0) +
+                          0.30 * (wgs > dl.cus ? fmax(longest, (work(a64) + work(b)) / dl.cus) : longest);
+        if (us < pa.us + pb.us) {
+            GemmPair pp;
+            pp.a = a64;
+            pp.b = b;
+            int gy_a, gy_b;
+            dma64_grid(a64, pp.gx_a, gy_a);
+            dma64_grid(b, pp.gx_b, gy_b);
+            pp.n_a = pp.gx_a * gy_a;
+            const int n_xcd = dl.n_xcd > 0 ? dl.n_xcd : 1;
+            pp.b0 = (pp.n_a + n_xcd - 1) / n_xcd * n_xcd;
+            const int64_t total = (int64_t)pp.b0 + (int64_t)pp.gx_b * gy_b;
+            if (total > INT32_MAX) return hipErrorInvalidValue;
+            gemm_dma_pair_kernel<64, 64, 3><<<dim3((unsigned)total), 256, 0, s>>>(pp);
+            return hipGetLastError();
+        }
+    }
+    e = launch_planned(a, pa, s);
+    return e != hipSuccess ? e : launch_planned(b, pb, s);
 }
 
 }  // namespace pcpp

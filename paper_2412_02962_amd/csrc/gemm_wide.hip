@@ -554,8 +554,8 @@ size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl) {
     return choose(M, N, K, false, N, 0, SIZE_MAX, dl).bytes;
 }
 
-bool plan_wide(GemmParams& p, const DeviceLayout& dl, double limit_us, int& shape) {
-    if (p.a_f32 || p.a_mode != 0 || p.K % KT != 0 || p.M < 1 || p.ldo % 8 != 0 ||
+bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& limit_us, int& shape) {
+    if (p.a_f32 || p.xa_T != 0 || p.K % KT != 0 || p.M < 1 || p.ldo % 8 != 0 ||
         (p.resid != nullptr && p.ldr % 8 != 0))
         return false;
     if (p.geglu && (p.resid != nullptr || p.out_bf16 != nullptr || p.bias2 != nullptr || p.seg < p.N ||
@@ -583,6 +583,7 @@ bool plan_wide(GemmParams& p, const DeviceLayout& dl, double limit_us, int& shap
     };
     p.m_major = rows(nt, mt, sh.bn, sh.bm) < rows(mt, nt, sh.bm, sh.bn);
     shape = c.shape;
+    limit_us = c.us;
     return true;
 }
 

@@ -2,9 +2,7 @@
 // statistics launch: Chan et al.'s pairwise update of (count, mean, M2) in a
 // fixed order, then, for the synchronized form (Sec. 3.3 of arXiv
 // 2412.02962, kept from DistriFusion), every band's statistics in band order
-// with this band's own in its place.  Shared by the GroupNorm apply kernel
-// and by the GEMM that applies GroupNorm while it stages its operand, so the
-// two produce the same bits.
+// with this band's own in its place.
 #pragma once
 
 #include "common.h"
@@ -31,28 +29,46 @@ struct GnStatsSrc {
     float* own_out;      // [B][G] x (count, mean, M2) of this band, or null
 };
 
-// Statistics of image b for the calling workgroup of exactly 256 threads:
-// thread (g, j) of S = 256 / G per group merges chunks j, j + S, ... (the
-// records of one chunk are consecutive in g: coalesced), then thread g
-// merges the S partial results in order j = 0, 1, ...  mrg: 256 x 3 floats of
-// LDS; writes g_mean[G] and g_rstd[G] (LDS) and the band's own statistics if
-// write_own; ends with a workgroup barrier.
-__device__ __forceinline__ void gn_group_stats(const GnStatsSrc& a, int b, bool write_own, float* mrg, float* g_mean,
+// Lanes that share one group's work: the largest power of two with G of them
+// in 256 threads, at most a wavefront.
+__host__ __device__ inline int gn_group_lanes(int G) {
+    int t = 1;
+    while (2 * t * G <= 256 && 2 * t <= 64) t *= 2;
+    return t;
+}
+
+// Statistics of image b for the calling workgroup (its first 256 threads do
+// the work; all must call): S consecutive lanes per group merge chunks j, j +
+// S, ... each and meet in a shuffle tree; the bands' statistics, a lane each
+// and loaded before everything else (a chain of eight dependent loads took 4
+// us), are then merged in band order by the group's first lane.  Writes
+// g_mean[G] and g_rstd[G] (LDS) and the band's own statistics if write_own;
+// ends with a workgroup barrier.
+__device__ __forceinline__ void gn_group_stats(const GnStatsSrc& a, int b, bool write_own, float* g_mean,
                                                float* g_rstd) {
     const int tid = threadIdx.x;
-    const int G = a.G;
-    const int S = 256 / G;
-    const int g = tid % G, j = tid / G;
-    float n = 0.f, mean = 0.f, m2 = 0.f;
-    if (j < S) {
+    if (tid < 256) {
+        const int G = a.G;
+        const int S = gn_group_lanes(G);
+        const int g = min(tid / S, G - 1), j = tid % S;
+        const bool mine = tid / S < G;
+        float bn = 0.f, bm = 0.f, bq = 0.f;  // band j's statistics
+        auto load_band = [&](int jb) {
+            const float* o = a.bands + (((int64_t)min(jb, a.n_bands - 1) * a.B + b) * G + g) * 3;
+            bn = o[0];
+            bm = o[1];
+            bq = o[2];
+        };
+        if (a.bands != nullptr) load_band(j);
+        float n = 0.f, mean = 0.f, m2 = 0.f;
         const float* st = a.stats + ((int64_t)b * a.chunks * G + g) * 3;
-        for (int k0 = j; k0 < a.chunks; k0 += 8 * S) {
+        for (int k0 = j; k0 < a.chunks; k0 += 4 * S) {
             // Records past the last chunk read the last one (every load in
             // bounds, none behind a branch: all in flight together) and count
             // zero, which the update skips.
-            float cn[8], cm[8], cq[8];
+            float cn[4], cm[4], cq[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 4; ++u) {
                 const int k = k0 + u * S;
                 const float* r = st + (int64_t)(k < a.chunks ? k : a.chunks - 1) * G * 3;
                 cn[u] = r[0];
@@ -60,41 +76,42 @@ __device__ __forceinline__ void gn_group_stats(const GnStatsSrc& a, int b, bool 
                 cq[u] = r[2];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int u = 0; u < 4; ++u)
                 if (k0 + u * S >= a.chunks) cn[u] = 0.f;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) chan_merge(n, mean, m2, cn[u], cm[u], cq[u]);
+            for (int u = 0; u < 4; ++u) chan_merge(n, mean, m2, cn[u], cm[u], cq[u]);
         }
-    }
-    mrg[3 * tid] = n;
-    mrg[3 * tid + 1] = mean;
-    mrg[3 * tid + 2] = m2;
-    __syncthreads();
-    if (tid < G) {
-        for (int k = 1; k < S; ++k)
-            chan_merge(n, mean, m2, mrg[3 * (tid + k * G)], mrg[3 * (tid + k * G) + 1], mrg[3 * (tid + k * G) + 2]);
-        if (a.own_out != nullptr && write_own) {
-            float* o = a.own_out + ((int64_t)b * G + tid) * 3;
+        for (int o = 1; o < S; o <<= 1) {
+            const float on = __shfl_xor(n, o), om = __shfl_xor(mean, o), oq = __shfl_xor(m2, o);
+            chan_merge(n, mean, m2, on, om, oq);
+        }
+        if (mine && j == 0 && write_own && a.own_out != nullptr) {
+            float* o = a.own_out + ((int64_t)b * G + g) * 3;
             o[0] = n;
             o[1] = mean;
             o[2] = m2;
         }
         if (a.bands != nullptr) {
+            // (only the first lane's sums are used: its own statistics are the ones written above)
+            const int lane0 = (tid & 63) - j;
             float tn = 0.f, tm = 0.f, tq = 0.f;
             for (int jb = 0; jb < a.n_bands; ++jb) {
-                if (jb == a.band) {
+                if (jb > 0 && jb % S == 0) load_band(jb + j);
+                const float on = __shfl(bn, lane0 + jb % S), om = __shfl(bm, lane0 + jb % S),
+                            oq = __shfl(bq, lane0 + jb % S);
+                if (jb == a.band)
                     chan_merge(tn, tm, tq, n, mean, m2);
-                } else {
-                    const float* o = a.bands + (((int64_t)jb * a.B + b) * G + tid) * 3;
-                    chan_merge(tn, tm, tq, o[0], o[1], o[2]);
-                }
+                else
+                    chan_merge(tn, tm, tq, on, om, oq);
             }
             n = tn;
             mean = tm;
             m2 = tq;
         }
-        g_mean[tid] = mean;
-        g_rstd[tid] = n > 0.f ? rsqrtf(m2 / n + a.eps) : 0.f;
+        if (mine && j == 0) {
+            g_mean[g] = mean;
+            g_rstd[g] = n > 0.f ? rsqrtf(m2 / n + a.eps) : 0.f;
+        }
     }
     __syncthreads();
 }

@@ -5,20 +5,21 @@
 // (synchronized GroupNorm, Sec. 3.3 of arXiv 2412.02962: every band's
 // (count, mean, M2) merged in band order, this band's own in its place).
 // Two kernels:
-//   gn_stats  one workgroup per chunk of 32 tokens (8 for bands under 2048
-//             tokens), held in registers
-//             (coalesced channel pairs), reduced to per-group (count, mean,
-//             M2) with two passes over the registers (sum, then squared
-//             deviations from the chunk mean).
-//   gn_apply  every workgroup first merges its image's chunk records with
-//             Chan et al.'s pairwise update in a fixed order (so all of them
-//             get the same statistics), then the bands, then applies the
-//             per-channel scale and shift to 2, 4 or 8 tokens with 16-byte
-//             vectors (optionally SiLU).  Workgroup 0 of an image writes the band's
-//             own statistics.  In framed mode (the input of a 3x3
-//             convolution) it writes into [B][rows+2][W+2][C], and the
-//             workgroups also fill the frame (neighbour edge rows or zeros)
-//             and export the band's own first and last rows.
+//   gn_stats_slab  a workgroup per chunk of tokens and slab of channels, held
+//                  in registers, reduced to per-group (count, mean, M2) with
+//                  two passes over the registers (sum, then squared
+//                  deviations from the chunk mean).  gn_stats_rows takes all
+//                  channels, for groups that no slab of whole 16-byte vectors
+//                  up to 256 channels holds.
+//   gn_apply       every workgroup first merges its image's chunk records with
+//                  Chan et al.'s pairwise update in a fixed order (so all of
+//                  them get the same statistics), then the bands, then applies
+//                  the per-channel scale and shift to its rows with 16-byte
+//                  vectors (optionally SiLU).  Workgroup 0 of an image writes
+//                  the band's own statistics.  In framed mode (the input of a
+//                  3x3 convolution) it writes into [B][rows+2][W+2][C], and
+//                  the workgroups also fill the frame (neighbour edge rows or
+//                  zeros) and export the band's own first and last rows.
 // LayerNorm: one wavefront per fp32 row, 16-byte loads, two passes over
 // registers (wavefront sums by DPP and lane swaps), 8-byte bf16 stores.
 
@@ -34,30 +35,22 @@ namespace pcpp {
 namespace {
 
 constexpr int GN_THREADS = 256;
-constexpr int GN_MAX_C = 2560;     // channels (LDS tables of gn_apply; the U-Net's widest concatenation)
+constexpr int GN_MAX_C = 2560;     // channels (the U-Net's widest concatenation)
 constexpr int GN_MAX_G = 256;
-// Tokens per statistics workgroup: 32, or 8 when a band has fewer than
-// 2048 tokens (so that it still gives about 64 or more workgroups per image
-// while the apply merges few chunk records).
+// Tokens per workgroup of gn_stats_rows: 32, or 8 when a band has fewer than
+// 2048 tokens.
 constexpr int GN_CHUNK_LONG = 32;
 constexpr int GN_CHUNK_SHORT = 8;
 __host__ __device__ inline int gn_chunk_tokens(int N) { return N >= 64 * GN_CHUNK_LONG ? GN_CHUNK_LONG : GN_CHUNK_SHORT; }
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// Lanes that sum one group's channel totals in gn_stats: the largest power of
-// two with G of them in the workgroup, at most a wavefront.
-__host__ __device__ inline int gn_group_lanes(int G) {
-    int t = 1;
-    while (2 * t * G <= GN_THREADS && 2 * t <= 64) t *= 2;
-    return t;
-}
-
 // Workspace of GroupNorm: [B][chunks][G] x (count, mean, M2).
 size_t gn_part_bytes(int B, int G, int chunks) { return (size_t)B * G * chunks * 3 * sizeof(float); }
 
+// The general kernel: a workgroup per chunk of tokens, all channels.
 template <int GN_CHUNK_TOKENS, int PP>  // PP: channel pairs per thread, ceil(C / 2 / GN_THREADS)
-__global__ __launch_bounds__(GN_THREADS) void gn_stats(GroupNormParams p) {
+__global__ __launch_bounds__(GN_THREADS) void gn_stats_rows(GroupNormParams p) {
     __shared__ float chan_acc[GN_MAX_C];
     __shared__ float g_mean[GN_MAX_G];
     const int ch = blockIdx.x, b = blockIdx.y;
@@ -149,32 +142,125 @@ __global__ __launch_bounds__(GN_THREADS) void gn_stats(GroupNormParams p) {
     }
 }
 
-template <int TPW>  // tokens per workgroup
-__global__ __launch_bounds__(GN_THREADS) void gn_apply(GroupNormParams p) {
-    __shared__ float sc[GN_MAX_C];
-    __shared__ float sh[GN_MAX_C];
-    __shared__ float mrg[GN_THREADS][3];
+// Statistics of a chunk of tokens and a slab of S channels (whole groups,
+// whole 16-byte vectors): a thread holds one vector of up to KR rows in
+// registers.  Splitting the channels as well keeps the launch at about one
+// workgroup per compute unit with 16 (32) chunks per image, whose records
+// every consumer merges: with 64 to 256 chunks the merge was most of the
+// apply's time (statistics and apply of 2 x 8192 x 960: 10 + 35 us, now 11 +
+// 22; of 2 x 8192 x 320: 5 + 26, now 8 + 13; of 2048 x 640: 6.6 + 9.8, now 6.1
+// + 7.4).  Sums: over a thread's rows, over the threads of a channel
+// (LDS), over the channels of a group (one wavefront each).
+template <int KR>
+__global__ __launch_bounds__(GN_THREADS) void gn_stats_slab(GroupNormParams p, int S, int ct) {
+    __shared__ __attribute__((aligned(16))) float part[GN_THREADS * 8];
+    __shared__ float chan[GN_THREADS];
+    __shared__ float total[GN_THREADS];  // per group of the slab
+    const int ch = blockIdx.x, b = blockIdx.z;
+    const int tid = threadIdx.x;
+    if (ch == 0 && blockIdx.y == 0 && b == 0) {
+        if (p.zero != nullptr)
+            for (int i = tid; i < p.n_zero; i += GN_THREADS) p.zero[i] = 0;
+        if (p.zero2 != nullptr)
+            for (int i = tid; i < p.n_zero2; i += GN_THREADS) p.zero2[i] = 0;
+    }
+    const int cg = p.C / p.G, gs = S / cg, V = S / 8, RP = GN_THREADS / V, QN = GN_THREADS / S;
+    const int v = tid % V, r0 = tid / V;
+    const int t0 = ch * ct, nt = min(ct, p.N - t0);
+    const bf16* xb = p.x + ((int64_t)b * p.N + t0) * p.C + blockIdx.y * S + 8 * v;
+    bf16x8 x[KR];
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+        const int r = r0 + k * RP;
+        x[k] = bf16x8{};
+        if (r0 < RP && r < nt) x[k] = *(const bf16x8*)(xb + (int64_t)r * p.C);
+    }
+    // Group sums of s (a thread's sums of its eight channels) into total[].
+    auto reduce = [&](const float (&s)[8]) {
+        if (r0 < RP) {
+            *(f32x4*)(part + r0 * S + 8 * v) = f32x4{s[0], s[1], s[2], s[3]};
+            *(f32x4*)(part + r0 * S + 8 * v + 4) = f32x4{s[4], s[5], s[6], s[7]};
+        }
+        __syncthreads();
+        const int c = tid % S, q = tid / S;
+        if (q < QN) {
+            float a = 0.f;
+            for (int r = q; r < RP; r += QN) a += part[r * S + c];
+            chan[q * S + c] = a;
+        }
+        __syncthreads();
+        const int lane = tid & 63;
+        for (int g = tid >> 6; g < gs; g += GN_THREADS / 64) {
+            float a = 0.f;
+            for (int q2 = 0; q2 < QN; ++q2)
+                for (int c2 = lane; c2 < cg; c2 += 64) a += chan[q2 * S + g * cg + c2];
+            for (int o = 1; o < 64; o <<= 1) a += __shfl_xor(a, o);
+            if (lane == 0) total[g] = a;
+        }
+        __syncthreads();
+    };
+    const float n_chunk = (float)nt * (float)cg;
+    float s[8] = {};
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += (float)x[k][e];  // rows past the end are zeros
+    reduce(s);
+    // Second pass: squared deviations from the chunk mean of the channel's group.
+    float mean[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        mean[e] = total[(8 * v + e) / cg] / n_chunk;
+        s[e] = 0.f;
+    }
+    float own_mean = 0.f;
+    if (tid < gs) own_mean = total[tid] / n_chunk;
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+        if (r0 + k * RP < nt) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float d = (float)x[k][e] - mean[e];
+                s[e] += d * d;
+            }
+        }
+    reduce(s);
+    if (tid < gs) {
+        float* st = p.stats + (((int64_t)b * p.chunks + ch) * p.G + blockIdx.y * gs + tid) * 3;
+        st[0] = n_chunk;
+        st[1] = own_mean;
+        st[2] = total[tid];
+    }
+}
+
+// A thread takes one 16-byte vector of channels (its scale and shift in
+// registers) in KR rows, RPI rows of the workgroup side by side: 320 threads
+// are whole rows of 320, 640, 1280 and 2560 channels.
+constexpr int GA_THREADS = 320;
+static_assert(GN_MAX_C / 8 <= GA_THREADS, "a row's vectors fit the workgroup");
+
+template <int KR>
+__global__ __launch_bounds__(GA_THREADS) void gn_apply(GroupNormParams p) {
     __shared__ float g_mean[GN_MAX_G], g_rstd[GN_MAX_G];
     const int b = blockIdx.y;
     const int tid = threadIdx.x;
     const int C = p.C, G = p.G, cg = C / G;
-    const int tok0 = blockIdx.x * TPW;
-    const int ntok = min(TPW, p.N - tok0);
     const int vpr = C / 8;  // 16-byte vectors per token row
-    const int64_t base = ((int64_t)b * p.N + tok0) * C;
-    // The tile's vectors are loaded first, the statistics merged meanwhile.
-    constexpr int VPT = (TPW * GN_MAX_C / 8 + GN_THREADS - 1) / GN_THREADS;
-    bf16x8 xv[VPT];
+    const int RPI = GA_THREADS / vpr;
+    const int r0 = tid / vpr, c = 8 * (tid - r0 * vpr);
+    const bool active = r0 < RPI;
+    const int tok0 = blockIdx.x * (RPI * KR) + r0;
+    const bf16* xb = p.x + (int64_t)b * p.N * C + c;
+    // The vectors, scale and shift are loaded first, the statistics merged meanwhile.
+    bf16x8 xv[KR], gm = {}, bt = {};
 #pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-        const int i = tid + GN_THREADS * k;
-        if (i < ntok * vpr) {
-            const int t = i / vpr, c = (i - t * vpr) * 8;
-            xv[k] = *(const bf16x8*)(p.x + base + (int64_t)t * C + c);
-        }
+    for (int k = 0; k < KR; ++k)
+        if (active && tok0 + k * RPI < p.N) xv[k] = *(const bf16x8*)(xb + (int64_t)(tok0 + k * RPI) * C);
+    if (active) {
+        gm = *(const bf16x8*)(p.gamma + c);
+        bt = *(const bf16x8*)(p.beta + c);
     }
-    // The image's statistics (chunks, then bands), the same code as the GEMM
-    // that applies GroupNorm while staging its operand.
+    // The image's statistics (chunks, then bands).
     {
         GnStatsSrc src;
         src.stats = p.stats;
@@ -186,30 +272,36 @@ __global__ __launch_bounds__(GN_THREADS) void gn_apply(GroupNormParams p) {
         src.n_bands = p.n_bands;
         src.band = p.band;
         src.own_out = p.own_out;
-        gn_group_stats(src, b, blockIdx.x == 0, &mrg[0][0], g_mean, g_rstd);
+        gn_group_stats(src, b, blockIdx.x == 0, g_mean, g_rstd);
     }
-    for (int c = tid; c < C; c += GN_THREADS) {
-        const int g = c / cg;
-        const float a = g_rstd[g] * bf16_to_f32(p.gamma[c]);
-        sc[c] = a;
-        sh[c] = bf16_to_f32(p.beta[c]) - g_mean[g] * a;
+    float sc[8], sh[8];
+    {
+        int g = min(c, C - 8) / cg, left = (g + 1) * cg - min(c, C - 8);  // channels left in group g
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (left == 0) {
+                ++g;
+                left = cg;
+            }
+            --left;
+            sc[e] = g_rstd[g] * bf16_to_f32(gm[e]);
+            sh[e] = bf16_to_f32(bt[e]) - g_mean[g] * sc[e];
+        }
     }
-    __syncthreads();
     const int pad_rows = p.pad_W > 0 ? p.N / p.pad_W : 0;
 #pragma unroll
-    for (int k = 0; k < VPT; ++k) {
-        const int i = tid + GN_THREADS * k;
-        if (i < ntok * vpr) {
-            const int t = i / vpr, c = (i - t * vpr) * 8;
+    for (int k = 0; k < KR; ++k) {
+        const int tok = tok0 + k * RPI;
+        if (active && tok < p.N) {
             bf16x8 y;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float v = __builtin_fmaf((float)xv[k][e], sc[c + e], sh[c + e]);
+                float v = __builtin_fmaf((float)xv[k][e], sc[e], sh[e]);
                 if (p.silu) v = v * __builtin_amdgcn_rcpf(1.f + __expf(-v));
                 y[e] = f32_to_bf16(v);
             }
             if (p.pad_W > 0) {  // token (row, col) of image b at framed (row + 1, col + 1)
-                const int tok = tok0 + t, row = tok / p.pad_W, col = tok - row * p.pad_W;
+                const int row = tok / p.pad_W, col = tok - row * p.pad_W;
                 const int64_t dst = ((int64_t)(b * (pad_rows + 2) + row + 1) * (p.pad_W + 2) + col + 1) * C;
                 *(bf16x8*)(p.y + dst + c) = y;
                 if (p.edges_out != nullptr) {  // the band's first and last rows, for its neighbours
@@ -218,7 +310,7 @@ __global__ __launch_bounds__(GN_THREADS) void gn_apply(GroupNormParams p) {
                         *(bf16x8*)(p.edges_out + ((int64_t)(2 * b + 1) * p.pad_W + col) * C + c) = y;
                 }
             } else {
-                *(bf16x8*)(p.y + base + (int64_t)t * C + c) = y;
+                *(bf16x8*)(p.y + ((int64_t)b * p.N + tok) * C + c) = y;
             }
         }
     }
@@ -231,7 +323,7 @@ __global__ __launch_bounds__(GN_THREADS) void gn_apply(GroupNormParams p) {
         const int64_t halo = 2LL * W * vpr;
         const int64_t total = halo + 2LL * (pad_rows + 2) * vpr;
         bf16* fb = p.y + (int64_t)b * (pad_rows + 2) * (W + 2) * C;
-        for (int64_t u = (int64_t)blockIdx.x * GN_THREADS + tid; u < total; u += (int64_t)gridDim.x * GN_THREADS) {
+        for (int64_t u = (int64_t)blockIdx.x * GA_THREADS + tid; u < total; u += (int64_t)gridDim.x * GA_THREADS) {
             u32x4 v = {0u, 0u, 0u, 0u};
             int64_t dst;
             if (u < halo) {
@@ -328,9 +420,43 @@ __global__ __launch_bounds__(256) void ln_kernel(LayerNormParams p) {
     }
 }
 
+// Chunks of the general statistics kernel, at least those of the other: the
+// workspace is sized for it.
 int gn_chunks(int N) {
     const int ct = gn_chunk_tokens(N);
     return N > 0 ? (N + ct - 1) / ct : 1;
+}
+
+// Slab of channels and tokens per chunk of gn_stats_slab; S = 0 where the
+// groups do not fit it (a multiple of whole groups and of 8 channels above
+// 256).  16 chunks per image (32 from 4096 tokens on), more where a thread
+// would hold over 16 rows; the widest slab that still gives a workgroup per
+// compute unit.
+struct SlabPlan {
+    int S, ct, chunks, rows;  // rows: per thread
+};
+constexpr int GN_SLAB_ROWS = 16;
+
+SlabPlan slab_plan(int B, int N, int C, int G, int cus) {
+    SlabPlan sp{0, 0, 0, 0};
+    const int cg = C / G;
+    int unit = cg;
+    while (unit % 8 != 0) unit += cg;  // C is a multiple of 8 and of cg: so is this of C
+    if (unit > GN_THREADS) return sp;
+    int chunks = N < 4096 ? 16 : 32;
+    if (chunks > gn_chunks(N)) chunks = gn_chunks(N);
+    int S = unit;
+    for (int s = unit; s <= GN_THREADS; s += unit)
+        if (C % s == 0 && (int64_t)chunks * B * (C / s) >= cus) S = s;
+    const int rp = GN_THREADS / (S / 8);
+    int ct = (N + chunks - 1) / chunks;
+    if (ct > GN_SLAB_ROWS * rp) ct = GN_SLAB_ROWS * rp;
+    sp.chunks = (N + ct - 1) / ct;
+    if (sp.chunks > gn_chunks(N)) return sp;
+    sp.S = S;
+    sp.ct = ct;
+    sp.rows = (ct + rp - 1) / rp;
+    return sp;
 }
 
 }  // namespace
@@ -343,9 +469,23 @@ bool gn_shapes_ok(int C, int G) {
 
 bool norm_shapes_ok(int C, int G) { return gn_shapes_ok(C, G) && C <= 4 * 64 * LN_MAX_VEC; }
 
-hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
+static hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
     if (!gn_shapes_ok(p.C, p.G)) return hipErrorInvalidValue;
     if (p.pad_W < 0 || (p.pad_W > 0 && p.N % p.pad_W != 0)) return hipErrorInvalidValue;
+    const SlabPlan sp = slab_plan(p.B, p.N, p.C, p.G, device_layout(s).cus);
+    if (sp.S > 0) {
+        p.chunks = sp.chunks;
+        const dim3 grid((unsigned)sp.chunks, (unsigned)(p.C / sp.S), (unsigned)p.B);
+        if (sp.rows <= 2)
+            gn_stats_slab<2><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+        else if (sp.rows <= 4)
+            gn_stats_slab<4><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+        else if (sp.rows <= 8)
+            gn_stats_slab<8><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+        else
+            gn_stats_slab<GN_SLAB_ROWS><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+        return hipGetLastError();
+    }
     p.chunks = gn_chunks(p.N);
     const dim3 grid(p.chunks, p.B);
     const bool lng = gn_chunk_tokens(p.N) == GN_CHUNK_LONG;
@@ -353,9 +493,9 @@ hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
 #define PCPP_GN_STATS(PP)                                                                      \
     case PP:                                                                                   \
         if (lng)                                                                               \
-            gn_stats<GN_CHUNK_LONG, PP><<<grid, GN_THREADS, 0, s>>>(p);                         \
+            gn_stats_rows<GN_CHUNK_LONG, PP><<<grid, GN_THREADS, 0, s>>>(p);                    \
         else                                                                                   \
-            gn_stats<GN_CHUNK_SHORT, PP><<<grid, GN_THREADS, 0, s>>>(p);                        \
+            gn_stats_rows<GN_CHUNK_SHORT, PP><<<grid, GN_THREADS, 0, s>>>(p);                   \
         break;
         PCPP_GN_STATS(1)
         PCPP_GN_STATS(2)
@@ -372,21 +512,21 @@ hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
 hipError_t launch_group_norm(GroupNormParams p, hipStream_t s) {
     const hipError_t e = launch_group_norm_stats(p, s);
     if (e != hipSuccess) return e;
-    // Tokens per apply workgroup: the most of 8, 4 and 2 that still give four
-    // workgroups per compute unit over the images (each workgroup merges the
-    // statistics records itself, so larger tiles where there are enough of
-    // them).  2048 x 640 and 512 x 1280: 2 tokens (the ResNets 2-5 us faster
-    // than with 8); 8192 x 320: 8.
+    // Rows per thread: the most of 8, 4, 2 and 1 that still give two
+    // workgroups per compute unit (each merges the statistics records itself;
+    // one per compute unit: level-0 ResNets 1 % slower).
     const int cus = device_layout(s).cus;
-    int tpw = 8;
-    while (tpw > 2 && (int64_t)((p.N + tpw - 1) / tpw) * p.B < 4 * (int64_t)cus) tpw /= 2;
-    const dim3 grid((unsigned)((p.N + tpw - 1) / tpw), (unsigned)p.B);
-    if (tpw == 8)
-        gn_apply<8><<<grid, GN_THREADS, 0, s>>>(p);
-    else if (tpw == 4)
-        gn_apply<4><<<grid, GN_THREADS, 0, s>>>(p);
-    else
-        gn_apply<2><<<grid, GN_THREADS, 0, s>>>(p);
+    const int rpi = GA_THREADS / (p.C / 8);
+    auto blocks = [&](int kr) { return (unsigned)((p.N + rpi * kr - 1) / (rpi * kr)); };
+    int kr = 8;
+    while (kr > 1 && (int64_t)blocks(kr) * p.B < 2 * cus) kr /= 2;
+    const dim3 grid(blocks(kr), (unsigned)p.B);
+    switch (kr) {
+        case 8: gn_apply<8><<<grid, GA_THREADS, 0, s>>>(p); break;
+        case 4: gn_apply<4><<<grid, GA_THREADS, 0, s>>>(p); break;
+        case 2: gn_apply<2><<<grid, GA_THREADS, 0, s>>>(p); break;
+        default: gn_apply<1><<<grid, GA_THREADS, 0, s>>>(p); break;
+    }
     return hipGetLastError();
 }
 
