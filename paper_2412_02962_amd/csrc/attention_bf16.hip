@@ -7,7 +7,8 @@
 // lies inside one source is fetched from that source's base; a tile that
 // straddles two sources (or the end) picks the source row by row.
 //
-// Work decomposition.  A block is 128 queries of one (image, head); its key
+// Work decomposition.  A block is 128 queries of one (image, head), or 256
+// where blocks are many (attention_wide.hip; make_plan has the rule); its key
 // tiles are cut into k equal pieces and a workgroup computes one piece of one
 // block.  Two workgroups share a compute unit (two wavefronts per SIMD, from
 // different workgroups, so that their tile barriers are independent), so a
@@ -55,84 +56,29 @@
 
 #include <math.h>
 
+#include "attention_bf16.h"
 #include "common.h"
 #include "kernels.h"
+#include "../../include/pcpp.h"
 
 namespace pcpp {
 
 namespace {
 
-constexpr int D = 64;
-constexpr int KT = 64;                      // keys per tile
+using namespace attn;
+
 constexpr int QW = 32;                      // queries per wavefront
 constexpr int NW = 4;                       // wavefronts per workgroup (one per SIMD)
 constexpr int QB = QW * NW;                 // queries per block
 constexpr int NTHREADS = 64 * NW;
 constexpr int WG_PER_CU = 8 / NW;           // two workgroups per compute unit: two wavefronts per SIMD
-constexpr int TILE_BYTES = KT * D * 2;      // 8 KB of K or of V
 constexpr int SLOTS = 4;                    // LDS slots for K tiles, and for V tiles
 constexpr int V_REGION = SLOTS * TILE_BYTES;
-constexpr float P_LIMIT = 1048576.0f;       // 2^20: bound on a lane's probability sum per half-tile
 constexpr int MIN_TILES_PER_PIECE = 3;
 
 constexpr int PIECES = TILE_BYTES / 1024 / NW;  // 1 KB pieces of a tile each wavefront stages
 static_assert(WG_PER_CU * 2 * V_REGION + 64 <= 160 * 1024, "the workgroups of a compute unit share its LDS");
 static_assert(PIECES >= 1 && PIECES * NW * 1024 == TILE_BYTES, "the wavefronts stage whole 1 KB pieces of a tile");
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef const __attribute__((address_space(1))) void* gptr_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
-
-// 16 bytes per lane from global memory straight into LDS: lane l's bytes land
-// at lds + 16 l (lds is the wave-uniform LDS byte address).  Written as inline
-// assembly so that the compiler does not track the LDS write: its own tracking
-// of such writes covers at most a few LDS buffers and otherwise waits for every
-// staging load in flight before any LDS read.  The kernel orders these writes
-// before the reads itself, with vmcnt waits and barriers.  Loads complete in
-// order, so the compiler's own vmcnt waits for register loads stay safe: they
-// only become more conservative.
-__device__ __forceinline__ void dma16(const void* g, const char* lds) {
-    const uint32_t a = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr_t)lds);
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(a) : "memory");
-}
-
-// The same with a wave-uniform 64-bit base in SGPRs and a 32-bit per-lane
-// byte offset (the load's saddr form): no per-lane address arithmetic.
-// lds is the wave-uniform LDS byte address.
-__device__ __forceinline__ void dma16_s(uint64_t base, uint32_t voff, uint32_t lds) {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
-}
-
-// A wave-uniform value known to the compiler as such (kept in SGPRs).
-__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// LDS swizzles: 16-byte chunk c of tile row r is stored at slot c ^ mask(r).
-// K rows are read 16 bytes per lane by 32 consecutive rows at one chunk; V
-// rows by four rows x 32 bytes per 16 lanes (transposing read).  Both masks
-// repeat every 16 rows, so a half-tile (32 rows) offset keeps them.
-__device__ __forceinline__ int k_mask(int r) { return (r >> 1) & 7; }
-__device__ __forceinline__ int v_mask(int r) { return ((r >> 1) & 3) << 1; }
-
-struct Sched {
-    int32_t n_xcd;      // XCDs; workgroup w runs on XCD w % n_xcd
-    int32_t bpx;        // blocks per XCD (the last XCD may hold fewer)
-    int32_t k;          // pieces per block
-    int32_t n_tiles;    // key tiles per block
-    int32_t nqb;        // blocks per (image, head)
-    int32_t n_blocks;   // blocks in total
-    int* counters;      // [n_blocks]: zero at launch, left zero (split launches only)
-    float* part_o;      // [grid][QB * D] partial outputs of pieces
-    float* part_ml;     // [grid][QB][2] their row statistics
-};
-
-__device__ __forceinline__ int64_t pick(int j, int end0, int end1, int64_t a0, int64_t a1, int64_t a2) {
-    const int64_t a12 = j < end1 ? a1 : a2;
-    return j < end0 ? a0 : a12;
-}
 
 // LDS operands of one pipeline step: K of a half-tile (four 16-byte chunks
 // per lane) and V^T of a half-tile (32-dim block mb, 16-key step st).
@@ -140,27 +86,6 @@ struct Operands {
     bf16x8 k[4];
     bf16x8 v[2][2];  // [mb][st]
 };
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-// Two transposing reads (rows p and p + 8 of a V tile) form one V^T operand.
-__device__ __forceinline__ bf16x8 read_vt(const char* p) {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 1024));
-    const short __attribute__((ext_vector_type(8))) w = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, w);
-}
-
-// Value of lanes l and l ^ 32 combined, without an LDS round trip.
-__device__ __forceinline__ float max_xor32(float v) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_xor32(float v) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
@@ -187,15 +112,7 @@ __global__ __launch_bounds__(NTHREADS, WG_PER_CU) void attn_bf16_kernel(AttnPara
     const int kv_end = p.kv.n_kv;
     const int end0 = p.kv.end0, end1 = p.kv.end1;
     const float sl2 = p.scale_log2;
-    // (1, 1) in a register the compiler cannot see through: the row-sum dots
-    // then take it as an operand, and the first dot of a half can take the
-    // inline constant 0 as its addend instead of a register cleared by a move.
-    bf16x2 ones = {(bf16)1.0f, (bf16)1.0f};
-    {
-        uint32_t ou = __builtin_bit_cast(uint32_t, ones);
-        asm volatile("" : "+v"(ou));
-        ones = __builtin_bit_cast(bf16x2, ou);
-    }
+    const bf16x2 ones = opaque_ones();
     const int n_tiles = sc.n_tiles;
 
     const int x = blockIdx.x % sc.n_xcd;
@@ -287,15 +204,14 @@ __global__ __launch_bounds__(NTHREADS, WG_PER_CU) void attn_bf16_kernel(AttnPara
         // Stage tile t of K (is_v = false) or V into the slot at dst.
         auto issue = [&](int t_in, char* slot, bool is_v) {
             const int t = __builtin_amdgcn_readfirstlane(t_in);
-            char* dst = slot + PIECES * wave * 1024;
+            const uint32_t dst = lds_of(slot);
             const uint32_t* off = is_v ? ld_voff : ld_koff;
             if (aligned) {
                 const uint64_t a0 = is_v ? sv0 : sk0, a1 = is_v ? sv1 : sk1, a2 = is_v ? sv2 : sk2;
                 const uint64_t src = t < tb0 ? a0 : (t < tb1 ? a1 : a2);
                 const uint64_t base = src + (uint64_t)(uint32_t)t * tile_g;
-                const uint32_t lds = lds_of(slot);
 #pragma unroll
-                for (int i = 0; i < PIECES; ++i) dma16_s(base, off[i], lds + i * 1024);
+                for (int i = 0; i < PIECES; ++i) dma16_s(base, off[i], dst + i * 1024);
                 return;
             }
             const int j0 = t * KT, j1 = j0 + KT;
@@ -396,14 +312,7 @@ __global__ __launch_bounds__(NTHREADS, WG_PER_CU) void attn_bf16_kernel(AttnPara
                 const bf16x2 pk = {f32_to_bf16(e0), f32_to_bf16(e1)};
                 p_cur[i >> 2][2 * (i & 3)] = pk[0];
                 p_cur[i >> 2][2 * (i & 3) + 1] = pk[1];
-                if (i == 0) {
-                    // the first pair starts the chain with the inline constant 0 as addend
-                    asm("v_dot2_f32_bf16 %0, %1, %2, 0"
-                        : "=v"(acc0)
-                        : "v"(__builtin_bit_cast(uint32_t, pk)), "v"(__builtin_bit_cast(uint32_t, ones)));
-                } else {
-                    acc0 = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, acc0, false);
-                }
+                acc0 = dot_sum(pk, ones, acc0, i == 0);
             };
             SCHED_FENCE();
             pair(0);
@@ -613,9 +522,11 @@ __global__ __launch_bounds__(NTHREADS, WG_PER_CU) void attn_bf16_kernel(AttnPara
 }
 
 struct Plan {
+    int32_t qb;  // queries per block
     int32_t n_xcd, bpx, k, grid, n_tiles, nqb, n_blocks;
     size_t off_counters, off_o, off_ml, ws_bytes;
     bool fits;
+    double us;  // estimated
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -634,6 +545,10 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //   Larger shapes: waves x (tiles per piece + 4), in tile times; they take
 //   several waves of smaller pieces rather than a ragged last wave of whole
 //   blocks.
+// us: the launch's time, for the choice between the two forms.  One wave: 6
+// and the cost above.  Several: 2 + waves x (1.05 x tiles + 7), within 5 % of
+// 45 us (2048 x 2662 x 20 heads), 127 (4096 x 10649 x 10), 257 (8192 x 10649
+// x 10) and 2830 (28800 x 37440 x 10), 8 % below 453 (7200 x 9360 x 20).
 constexpr int64_t TILE_COST_SHARED = 100;
 constexpr int64_t TILE_COST_ALONE = 64;
 constexpr int64_t PIECE_COST = 257;
@@ -641,11 +556,11 @@ constexpr int64_t SHARED_CU_COST = 183;
 constexpr int64_t PIECE_COST_TILES = 4;
 constexpr int64_t MAX_SPLIT_BLOCKS = 65536;  // work counters kept at a fixed place
 
-int64_t pick_k(int64_t slots, int64_t cus, int64_t n_tiles) {
+int64_t pick_k(int64_t slots, int64_t cus, int64_t n_tiles, double* us) {
     const int64_t max_grid = (int64_t)WG_PER_CU * cus;
     const int64_t k_max = n_tiles / MIN_TILES_PER_PIECE;
     const bool one_wave = slots <= max_grid;
-    int64_t best_k = 1, best = -1;
+    int64_t best_k = 1, best = -1, best_waves = 1, best_tiles = 0;
     for (int64_t k = 1; k == 1 || (k <= k_max && k <= 64); ++k) {
         const int64_t w = slots * k;
         const int64_t waves = (w + max_grid - 1) / max_grid;
@@ -661,6 +576,33 @@ int64_t pick_k(int64_t slots, int64_t cus, int64_t n_tiles) {
         if (best < 0 || cost < best) {
             best = cost;
             best_k = k;
+            best_waves = waves;
+            best_tiles = tiles;
+        }
+    }
+    *us = one_wave ? 6.0 + 0.0109 * (double)best : 2.0 + (double)best_waves * (1.05 * (double)best_tiles + 7.0);
+    return best_k;
+}
+
+// The same for the 256-query form, in microseconds: a tile takes 1.88 with
+// two workgroups on a compute unit and 1.2 with one (the last round's, where
+// they fit), a workgroup's ends 4, a launch 5; a split adds its merge and the
+// write-back of 64 KB per workgroup at the end of the launch.  Within 3 % of
+// 44, 126, 246 (k = 4; 253 with the 3 that it takes), 2665 and 379 us at the
+// sizes above.  max_pieces: workgroups whose partial results fit the
+// workspace.
+int64_t pick_k_wide(int64_t slots, int64_t cus, int64_t n_tiles, int64_t max_pieces, double* us) {
+    const int64_t round = 2 * cus;
+    int64_t best_k = 1;
+    *us = 1e30;
+    for (int64_t k = 1; k == 1 || (k <= 64 && n_tiles / k >= MIN_TILES_PER_PIECE && slots * k <= max_pieces); ++k) {
+        const int64_t w = slots * k, rem = w % round;
+        const double tiles = (double)((n_tiles + k - 1) / k);
+        double t = 5.0 + (double)(w / round) * (tiles * 1.88 + 4.0) + (k > 1 ? 3.0 + 0.0135 * (double)w : 0.0);
+        if (rem > 0) t += tiles * (rem <= cus ? 1.2 : 1.88) + 4.0;
+        if (t < *us) {
+            *us = t;
+            best_k = k;
         }
     }
     return best_k;
@@ -673,16 +615,24 @@ int64_t pick_k(int64_t slots, int64_t cus, int64_t n_tiles) {
 // need no clearing.  Pieces are merged only where the device layout says
 // that workgroup w runs on XCD w % n_xcd; otherwise every workgroup
 // computes whole blocks.
-Plan make_plan(const AttnParams& p, const DeviceLayout& d) {
+// max_pieces: for the 256-query form, see above.
+Plan make_form(const AttnParams& p, const DeviceLayout& d, int qb, int64_t max_pieces) {
     Plan pl;
+    pl.qb = qb;
     pl.n_tiles = (p.kv.n_kv + KT - 1) / KT;
-    pl.nqb = (p.nq + QB - 1) / QB;
+    pl.nqb = (p.nq + qb - 1) / qb;
     const int64_t n_blocks = (int64_t)p.batch * p.heads * pl.nqb;
     pl.n_blocks = (int32_t)(n_blocks < INT32_MAX ? n_blocks : INT32_MAX);
     pl.n_xcd = d.xcd_merge ? d.n_xcd : 1;
     const int64_t bpx = (n_blocks + pl.n_xcd - 1) / pl.n_xcd;
     int64_t k = 1;
-    if (d.xcd_merge && n_blocks <= MAX_SPLIT_BLOCKS) k = pick_k(pl.n_xcd * bpx, d.cus, pl.n_tiles);
+    const bool split = d.xcd_merge && n_blocks <= MAX_SPLIT_BLOCKS;
+    if (qb == WIDE_QUERIES) {
+        k = pick_k_wide(pl.n_xcd * bpx, d.cus, pl.n_tiles, split ? max_pieces : 0, &pl.us);
+    } else {
+        k = pick_k(pl.n_xcd * bpx, d.cus, pl.n_tiles, &pl.us);
+        if (!split) k = 1;
+    }
     pl.k = (int32_t)k;
     pl.bpx = (int32_t)(bpx < INT32_MAX ? bpx : INT32_MAX);
     const int64_t grid = (int64_t)pl.n_xcd * bpx * k;
@@ -693,11 +643,29 @@ Plan make_plan(const AttnParams& p, const DeviceLayout& d) {
     pl.off_counters = off;
     off += align256((size_t)MAX_SPLIT_BLOCKS * sizeof(int));
     pl.off_o = off;
-    off += align256(pieces * QB * D * sizeof(float));
+    off += align256(pieces * qb * D * sizeof(float));
     pl.off_ml = off;
-    off += align256(pieces * QB * 2 * sizeof(float));
+    off += align256(pieces * qb * 2 * sizeof(float));
     pl.ws_bytes = off;
     return pl;
+}
+
+// Blocks of 256 queries where the estimate is 4 % below that of blocks of 128
+// (the estimates' own error): 443 -> 379 us at 7200 x 9360 x 20 heads, 2797
+// -> 2665 at 28800 x 37440 x 10, 254 -> 246 at 8192 x 10649 x 10; not at 2048
+// x 3072 x 10, batch 2 (47.4 and 47.6), and not where the blocks do not fill
+// the compute units twice (2048 x 2662 x 10: 23.7 and 29.1).
+// Its partial results get the other form's workspace.  Only where that is
+// past pcpp_partial_attention_noalloc's limit anyway it may grow, by the
+// blocks that rounding up to 256 queries adds.
+Plan make_plan(const AttnParams& p, const DeviceLayout& d) {
+    const Plan pl = make_form(p, d, QB, 0);
+    int64_t max_pieces = pl.k > 1 ? (int64_t)pl.grid * QB / WIDE_QUERIES : 0;
+    if (pl.ws_bytes > (size_t)PCPP_NOALLOC_SCRATCH_BYTES) max_pieces += (int64_t)pl.n_xcd * pl.k;
+    Plan wide = make_form(p, d, WIDE_QUERIES, max_pieces);
+    if (!d.xcd_merge || !wide.fits || wide.us >= 0.96 * pl.us) return pl;
+    if (wide.ws_bytes < pl.ws_bytes) wide.ws_bytes = pl.ws_bytes;
+    return wide;
 }
 
 }  // namespace
@@ -708,7 +676,7 @@ size_t attention_bf16_counter_bytes() { return align256((size_t)MAX_SPLIT_BLOCKS
 
 AttnPlanInfo attention_bf16_plan(const AttnParams& p, const DeviceLayout& d) {
     const Plan pl = make_plan(p, d);
-    return AttnPlanInfo{QB, pl.k, pl.grid, pl.k > 1 ? pl.n_blocks : 0};
+    return AttnPlanInfo{pl.qb, pl.k, pl.grid, pl.k > 1 ? pl.n_blocks : 0};
 }
 
 hipError_t launch_attention_bf16(const AttnParams& p, void* ws, size_t ws_bytes, hipStream_t stream) {
@@ -725,6 +693,7 @@ hipError_t launch_attention_bf16(const AttnParams& p, void* ws, size_t ws_bytes,
     sc.counters = (int*)((char*)ws + pl.off_counters);
     sc.part_o = (float*)((char*)ws + pl.off_o);
     sc.part_ml = (float*)((char*)ws + pl.off_ml);
+    if (pl.qb == WIDE_QUERIES) return launch_attention_wide(p, sc, pl.grid, stream);
     attn_bf16_kernel<<<pl.grid, NTHREADS, 0, stream>>>(p, sc);
     return hipGetLastError();
 }
