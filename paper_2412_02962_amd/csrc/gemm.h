@@ -67,7 +67,7 @@ struct GemmParams {
     int64_t xa_ldkv = 0;
     // Set by launch_gemm for a split launch.
     int32_t splitk = 1, n_xcd = 1, tpx = 0, n_tiles = 0;
-    int32_t m_major = 0;  // wide tiles: all W tiles of one token tile together
+    int32_t m_group = 1;  // wide tiles: token tiles whose W tiles are walked together
 };
 constexpr int GEMM_XA_MAXT = 96;  // keys of the cross-attention epilogue
 

@@ -117,16 +117,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_wide_kernel(GemmParams p) {
     const int tile = xcd * p.tpx + tl;
     if (tl >= p.tpx || tile >= p.n_tiles) return;  // idle slot of the last XCD (uniform)
     constexpr int BNO = GEGLU ? BN / 2 : BN;  // outputs per tile
-    int m_tile, n_tile;
-    if (p.m_major) {
-        const int nt = p.N / BNO;
-        m_tile = tile / nt;
-        n_tile = tile - m_tile * nt;
-    } else {
-        const int mt = (p.M + BM - 1) / BM;
-        n_tile = tile / mt;
-        m_tile = tile - n_tile * mt;
-    }
+    // groups of m_group token tiles, n-major within a group
+    const int mt = (p.M + BM - 1) / BM;
+    const int grp = tile / (p.m_group * (p.N / BNO));
+    const int in_grp = tile - grp * (p.m_group * (p.N / BNO));
+    const int gm = min(p.m_group, mt - grp * p.m_group);
+    const int n_tile = in_grp / gm;
+    const int m_tile = grp * p.m_group + (in_grp - n_tile * gm);
     const int m0 = m_tile * BM, n0 = n_tile * BNO;
     const int nk_all = p.K / KT;
     const int kt0 = (int)((int64_t)nk_all * piece / p.splitk);
@@ -575,13 +572,19 @@ bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& limit_us, int& sha
     p.splitk = c.splitk;
     p.n_xcd = dl.xcd_merge ? dl.n_xcd : 1;
     p.tpx = (p.n_tiles + p.n_xcd - 1) / p.n_xcd;
-    // Order of the tiles: the one whose range of tpx tiles on an XCD covers
-    // fewer rows of X and W, which its L2 takes in.
-    auto rows = [&](int inner, int outer, int b_inner, int b_outer) {
-        const int in = p.tpx < inner ? p.tpx : inner, out = (p.tpx + inner - 1) / inner;
-        return (int64_t)in * b_inner + (int64_t)(out < outer ? out : outer) * b_outer;
-    };
-    p.m_major = rows(nt, mt, sh.bn, sh.bm) < rows(mt, nt, sh.bm, sh.bn);
+    // Order of the tiles: groups of token tiles whose range of tpx tiles on an
+    // XCD covers the fewest rows of X and W, which its L2 takes in.
+    int64_t fewest = INT64_MAX;
+    for (int g = 1; g <= mt && g <= 64; g = g < mt && 2 * g > mt ? mt : 2 * g) {
+        const int64_t per = (int64_t)g * nt;  // tiles of a group
+        const int64_t mr = p.tpx <= g ? p.tpx : g * ((p.tpx + per - 1) / per);
+        const int64_t nr = p.tpx >= per ? nt : (p.tpx + g - 1) / g;
+        const int64_t rows = (mr < mt ? mr : mt) * sh.bm + nr * sh.bn;
+        if (rows < fewest) {
+            fewest = rows;
+            p.m_group = g;
+        }
+    }
     shape = c.shape;
     limit_us = c.us;
     return true;
