@@ -32,6 +32,26 @@ struct IC {
     static constexpr int value = V;
 };
 
+// Output of column n (at most three segments) and its place in the segment.
+// Compares and selects: an index computed per lane makes the compiler fetch
+// p.out[.] from the kernel's arguments with a vector load before every store,
+// and wait for it behind the store before.
+__device__ __forceinline__ void* out_segment(const GemmParams& p, int n, int& ns) {
+    void* const o0 = p.out[0];
+    void* const o1 = p.out[1];
+    void* const o2 = p.out[2];
+    const bool in1 = n >= p.seg, in2 = n >= 2 * (int64_t)p.seg;
+    ns = in2 ? n - 2 * p.seg : in1 ? n - p.seg : n;
+    return in2 ? o2 : in1 ? o1 : o0;
+}
+
+// The same for segments seg_stride elements apart.
+__device__ __forceinline__ void* strided_segment(const GemmParams& p, int n, int& ns) {
+    const int seg = n / p.seg;
+    ns = n - seg * p.seg;
+    return (char*)p.out[0] + (int64_t)seg * p.seg_stride * (p.out_f32 ? 4 : 2);
+}
+
 template <int WMB, int WNB, bool AF32>
 __global__ __launch_bounds__(256) void gemm_kernel(GemmParams p) {
     constexpr int BM = 2 * 32 * WMB;           // tokens per workgroup
@@ -203,9 +223,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmParams p) {
                         for (int e = 0; e < 4; ++e) v[e] += bf16_to_f32(rv[e]);
                     }
                 }
-                const int seg = n / p.seg;
-                const int ns = n - seg * p.seg;
-                void* dst = p.out[seg];
+                int ns;
+                void* dst = out_segment(p, n, ns);
                 if (p.out_f32) {
                     f32x4 o = {v[0], v[1], v[2], v[3]};
                     *(f32x4*)((float*)dst + (int64_t)m * p.ldo + ns) = o;
@@ -557,6 +576,46 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
     };
 
+    // Epilogue: lane holds token (m-block base + col) and W rows
+    // (n-block base + 8c + 4*half + 0..3) in registers 4c..4c+3.  Bias and
+    // residual are loaded here, behind the products (of a split tile, only by
+    // the piece that finishes it): after them the loads' trip to memory adds
+    // to every launch (512 x 1280 x 1280 with a float32 residual 11.8 -> 11.7
+    // us, with the selects of out_segment).
+    auto n_of = [&](int i, int c) { return n0 + (BN / 2) * wn + 32 * i + 8 * c + 4 * half; };
+    auto m_of = [&](int j) { return m0 + (BM / 2) * wm + 32 * j + col; };
+    bf16x4 bias_v[WNB][4] = {}, res_h[WNB][WMB][4] = {};
+    f32x4 res_v[WNB][WMB][4] = {}, bias2_v[WNB][WMB][4] = {};
+    auto load_addends = [&]() {
+        auto each = [&](auto f) {
+#pragma unroll
+            for (int i = 0; i < WNB; ++i)
+#pragma unroll
+                for (int j = 0; j < WMB; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) f(i, j, c, min(m_of(j), p.M - 1), n_of(i, c));
+        };
+        if (p.bias != nullptr)
+            each([&](int i, int j, int c, int, int n) {
+                if (j == 0) bias_v[i][c] = *(const bf16x4*)(p.bias + n);
+            });
+        if (p.resid != nullptr && p.resid_f32)
+            each([&](int i, int j, int c, int m, int n) {
+                res_v[i][j][c] = *(const f32x4*)((const float*)p.resid + (int64_t)m * p.ldr + n);
+            });
+        if (p.resid != nullptr && !p.resid_f32)
+            each([&](int i, int j, int c, int m, int n) {
+                res_h[i][j][c] = *(const bf16x4*)((const bf16*)p.resid + (int64_t)m * p.ldr + n);
+            });
+        if (p.bias2 != nullptr)
+            each([&](int i, int j, int c, int m, int n) {
+                bias2_v[i][j][c] = *(const f32x4*)(p.bias2 + (int64_t)(m / p.bias2_rows) * p.N + n);
+            });
+    };
+    if constexpr (!XATT) {
+        if (p.splitk == 1) load_addends();
+    }
+
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
         if (kt0 + s < kt1) issue(kt0 + s, s);
@@ -631,48 +690,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
     }
 
-    // Epilogue: lane holds token (m-block base + col) and W rows
-    // (n-block base + 8c + 4*half + 0..3) in registers 4c..4c+3.  All bias
-    // and residual loads are issued before the first store: the output may
-    // be the residual buffer itself (an in-place update, each element read
-    // and written by the same lane), so the compiler could not move a load
-    // above an earlier store.
-    auto n_of = [&](int i, int c) {
-        return n0 + (BN / 2) * wn + 32 * i + 8 * c + 4 * half;
-    };
-    auto m_of = [&](int j) { return m0 + (BM / 2) * wm + 32 * j + col; };
-    float bias_v[WNB][4][4];
-    f32x4 res_v[WNB][WMB][4];
-#pragma unroll
-    for (int i = 0; i < WNB; ++i)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int n = n_of(i, c);
-            bf16x4 bv = {};
-            if (p.bias != nullptr) bv = *(const bf16x4*)(p.bias + n);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bias_v[i][c][e] = bf16_to_f32(bv[e]);
-#pragma unroll
-            for (int j = 0; j < WMB; ++j) {
-                const int m = min(m_of(j), p.M - 1);
-                f32x4 rv = {0.f, 0.f, 0.f, 0.f};
-                if (p.resid != nullptr) {
-                    if (p.resid_f32) {
-                        rv = *(const f32x4*)((const float*)p.resid + (int64_t)m * p.ldr + n);
-                    } else {
-                        const bf16x4 rb = *(const bf16x4*)((const bf16*)p.resid + (int64_t)m * p.ldr + n);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) rv[e] = bf16_to_f32(rb[e]);
-                    }
-                }
-                if (p.bias2 != nullptr) {
-                    const f32x4 b2 = *(const f32x4*)(p.bias2 + (int64_t)(m / p.bias2_rows) * p.N + n);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) rv[e] += b2[e];
-                }
-                res_v[i][j][c] = rv;
-            }
-        }
+    if (p.splitk > 1) load_addends();
 #pragma unroll
     for (int i = 0; i < WNB; ++i) {
 #pragma unroll
@@ -684,14 +702,13 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
                 const int n = n_of(i, c);
                 float v[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * c + e] + bias_v[i][c][e];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += res_v[i][j][c][e];
-                const int seg = n / p.seg;
-                const int ns = n - seg * p.seg;
-                void* dst = p.seg_stride > 0
-                                ? (void*)((char*)p.out[0] + (int64_t)seg * p.seg_stride * (p.out_f32 ? 4 : 2))
-                                : p.out[seg];
+                for (int e = 0; e < 4; ++e) {
+                    float rv = p.resid_f32 ? res_v[i][j][c][e] : bf16_to_f32(res_h[i][j][c][e]);
+                    if (p.bias2 != nullptr) rv += bias2_v[i][j][c][e];
+                    v[e] = (acc[i][j][4 * c + e] + bf16_to_f32(bias_v[i][c][e])) + rv;
+                }
+                int ns;
+                void* dst = p.seg_stride > 0 ? strided_segment(p, n, ns) : out_segment(p, n, ns);
                 if (p.out_f32) {
                     f32x4 o = {v[0], v[1], v[2], v[3]};
                     *(f32x4*)((float*)dst + (int64_t)m * p.ldo + ns) = o;
@@ -809,6 +826,33 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
 #pragma unroll
     for (int fb = 0; fb < 5; ++fb) acc[fb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // Wavefront (tb, 0) finishes blocks 0-2, (tb, 1) blocks 3-4: token
+    // m0 + 16 tb + lane % 16, W rows n0 + 16 fb + 4 (lane / 16) + 0..3.  Their
+    // bias and residual are loaded here, behind the products: after them the
+    // loads' trip to memory adds to every launch (1024 x 1280 x 1280 with a
+    // float32 residual 11.96 -> 11.56 us, 4096 x 640 x 640 13.8 -> 13.1).
+    auto owned = [&](int fb) { return kg == 0 ? fb < 3 : fb >= 3; };
+    const int m = m0 + 16 * tb + (lane & 15);
+    const int mc = min(m, p.M - 1);
+    bf16x4 bias_v[3] = {}, res_h[3] = {};
+    f32x4 res_v[3] = {};
+    const int nl = n0 + 4 * (lane >> 4);
+    auto row_of = [&](int i) { return nl + 16 * min(3 * kg + i, 4); };  // (tb, 1): its second block twice
+    if (p.bias != nullptr) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) bias_v[i] = *(const bf16x4*)(p.bias + row_of(i));
+    }
+    if (p.resid != nullptr && p.resid_f32) {
+        const float* r = (const float*)p.resid + (int64_t)mc * p.ldr;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) res_v[i] = *(const f32x4*)(r + row_of(i));
+    }
+    if (p.resid != nullptr && !p.resid_f32) {
+        const bf16* r = (const bf16*)p.resid + (int64_t)mc * p.ldr;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) res_h[i] = *(const bf16x4*)(r + row_of(i));
+    }
+
 #pragma unroll
     for (int st = 0; st < NS - 1; ++st)
         if (st < nk) issue(st, st);
@@ -839,11 +883,10 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
         acc[4] = mfma16x16x32(__builtin_bit_cast(bf16x8, w4), __builtin_bit_cast(bf16x8, x), acc[4]);
     }
 
-    // The two k-steps' sums: wavefront (tb, 0) finishes blocks 0-2, (tb, 1)
-    // blocks 3-4; each hands the other its sums of the other's blocks.
+    // The two k-steps' sums: each wavefront hands its partner the sums of the
+    // partner's blocks.
     __syncthreads();  // every wavefront is past its last LDS operand read
     float* red = (float*)lds;  // [tb][block][lane] x 4 floats (20 KB)
-    auto owned = [&](int fb) { return kg == 0 ? fb < 3 : fb >= 3; };
 #pragma unroll
     for (int fb = 0; fb < 5; ++fb)
         if (!owned(fb)) *(f32x4*)(red + ((tb * 5 + fb) * 64 + lane) * 4) = acc[fb];
@@ -852,49 +895,26 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
     for (int fb = 0; fb < 5; ++fb)
         if (owned(fb)) acc[fb] += *(const f32x4*)(red + ((tb * 5 + fb) * 64 + lane) * 4);
 
-    // Epilogue: token m0 + 16 tb + lane % 16, W rows n0 + 16 fb + 4 (lane / 16)
-    // + 0..3; all bias and residual loads before the first store (the output
-    // may be the residual buffer itself).
-    const int m = m0 + 16 * tb + (lane & 15);
-    const int mc = min(m, p.M - 1);
-    // The epilogue keeps the order of the 64 x 64 kernel: (acc + bias) + residual.
-    f32x4 bias_v[5], res_v[5];
-#pragma unroll
-    for (int fb = 0; fb < 5; ++fb) {
-        bias_v[fb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        res_v[fb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (!owned(fb)) continue;
-        const int n = n0 + 16 * fb + 4 * (lane >> 4);
-        if (p.bias != nullptr) {
-            const bf16x4 bv = *(const bf16x4*)(p.bias + n);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bias_v[fb][e] = bf16_to_f32(bv[e]);
-        }
-        if (p.resid != nullptr) {
-            if (p.resid_f32) {
-                res_v[fb] = *(const f32x4*)((const float*)p.resid + (int64_t)mc * p.ldr + n);
-            } else {
-                const bf16x4 rb = *(const bf16x4*)((const bf16*)p.resid + (int64_t)mc * p.ldr + n);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) res_v[fb][e] = bf16_to_f32(rb[e]);
-            }
-        }
-    }
     if (m >= p.M) return;
-    const int sg = n0 / p.seg;  // output segment of the whole tile (80 divides the segment width)
+    int ns0;
+    void* const dst = out_segment(p, n0, ns0);  // of the whole tile (80 divides the segment width)
 #pragma unroll
     for (int fb = 0; fb < 5; ++fb) {
         if (!owned(fb)) continue;
-        const int n = n0 + 16 * fb + 4 * (lane >> 4);
+        const int n = nl + 16 * fb;
         float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (acc[fb][e] + bias_v[fb][e]) + res_v[fb][e];
-        const int ns = n - sg * p.seg;
+        for (int e = 0; e < 4; ++e) {  // the 64 x 64 kernel's order; one of the two residuals is zero
+            const int i = fb % 3;
+            const float res = p.resid_f32 ? res_v[i][e] : bf16_to_f32(res_h[i][e]);
+            v[e] = (acc[fb][e] + bf16_to_f32(bias_v[i][e])) + res;
+        }
+        const int ns = ns0 + (n - n0);
         if (p.out_f32) {
-            *(f32x4*)((float*)p.out[sg] + (int64_t)m * p.ldo + ns) = f32x4{v[0], v[1], v[2], v[3]};
+            *(f32x4*)((float*)dst + (int64_t)m * p.ldo + ns) = f32x4{v[0], v[1], v[2], v[3]};
         } else {
             const bf16x4 o = {f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};
-            *(bf16x4*)((bf16*)p.out[sg] + (int64_t)m * p.ldo + ns) = o;
+            *(bf16x4*)((bf16*)dst + (int64_t)m * p.ldo + ns) = o;
         }
         if (p.out_bf16 != nullptr) {
             const bf16x4 o = {f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};
