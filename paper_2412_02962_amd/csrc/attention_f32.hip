@@ -7,7 +7,7 @@
 // weighted sum of values are float64 (the float32 inputs widen exactly), so
 // the only float32 rounding is the final store.
 //
-// Bound by the float64 matrix rate (60 TFLOP/s in a large product).  A
+// Bound by the float64 matrix rate (73 TFLOP/s in a large library product).  A
 // workgroup computes 16 queries of one (image, head); its wavefronts take
 // consecutive ranges of the 16-key tiles and their results meet in LDS.  Both
 // products run on 16x16x4 float64 MFMAs, transposed (S^T = K Q^T, O^T = V^T
@@ -17,7 +17,7 @@
 // dimensions 16 g .. 16 g + 15 of K and Q, and value row lane % 16 of block
 // db is head dimension 4 (lane % 16) + db.  K and V go straight from the L2
 // into registers, a tile ahead: 16 queries per read of a key give 8 flops a
-// byte, 7.5 TB/s at the full rate, well under the 18 TB/s of the L2.
+// byte, 9 TB/s at the full rate, half of the 18 TB/s of the L2.
 // The matrix and the vector unit share the float64 multipliers, so that a
 // tile's exponentials and conversions (about 1000 cycles a wavefront) add to
 // its 2048 cycles of products.  256 queries x 640 keys x 20 heads: 1163 us
