@@ -622,6 +622,15 @@ int pcpp_conv3x3_export(const pcpp_conv_geom_t* g, const void* x,
                         void* stream);
 
 /*
+ * Launch plan of the convolution's product (host only, no GPU work; for
+ * diagnostics and tests); cus, cus_enabled and stream as for
+ * pcpp_partial_attention_plan.  Outputs (any may be NULL): tokens and outputs
+ * of a workgroup's tile and the pieces its k = 9 c_in is split into.
+ */
+int pcpp_conv3x3_plan(const pcpp_conv_geom_t* g, int32_t cus, int32_t cus_enabled, void* stream,
+                      int32_t* tile_tokens, int32_t* tile_outputs, int32_t* pieces);
+
+/*
  * [rows, ca] and [rows, cb] bf16 side by side into out [rows, ca + cb]: the
  * U-Net up path's concatenation of a level's state with its skip connection
  * (the ResNet that follows takes ca + cb channels).  b = NULL fills the cb

@@ -112,6 +112,35 @@ int validate_conv(const pcpp_conv_geom_t* g) {
     return PCPP_OK;
 }
 
+// The convolution as a product: one token per output, k = 9 c_in.
+GemmParams conv_params(const pcpp_conv_geom_t* g, const ConvLayout& L, const void* framed, const void* w,
+                       const void* bias, void* y) {
+    GemmParams p;
+    p.a = framed;
+    p.lda = 0;
+    p.a_f32 = 0;
+    p.w = (const __bf16*)w;
+    p.bias = (const __bf16*)bias;
+    p.M = g->batch * L.ho * L.wo;
+    p.N = g->c_out;
+    p.K = 9 * g->c_in;
+    p.geglu = 0;
+    p.F = 0;
+    p.resid = nullptr;
+    p.ldr = 0;
+    p.resid_f32 = 0;
+    p.out[0] = y;
+    p.out[1] = p.out[2] = nullptr;
+    p.seg = g->c_out;
+    p.ldo = g->c_out;
+    p.out_f32 = 0;
+    p.out_bf16 = nullptr;
+    p.conv_W = L.Wf;
+    p.conv_rows = L.Hf;
+    p.conv_stride = g->mode == PCPP_CONV_DOWN ? 2 : 1;
+    return p;
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
@@ -128,6 +157,21 @@ using namespace pcpp;
 PCPP_EXPORT size_t pcpp_conv3x3_workspace_size(const pcpp_conv_geom_t* g) {
     if (validate_conv(g) != PCPP_OK) return 0;
     return conv_layout(g).total;
+}
+
+PCPP_EXPORT int pcpp_conv3x3_plan(const pcpp_conv_geom_t* g, int32_t cus, int32_t cus_enabled, void* stream,
+                                  int32_t* tile_tokens, int32_t* tile_outputs, int32_t* pieces) {
+    const int st = validate_conv(g);
+    if (st != PCPP_OK) return st;
+    DeviceLayout d;
+    if (!layout_of_query(cus, cus_enabled, (hipStream_t)stream, &d)) return cus == 0 ? PCPP_EHIP : PCPP_EINVAL;
+    GemmPlanInfo info;
+    if (gemm_plan_info(conv_params(g, conv_layout(g), nullptr, nullptr, nullptr, nullptr), d, &info) != hipSuccess)
+        return PCPP_ENOTSUP;
+    if (tile_tokens) *tile_tokens = info.tile_tokens;
+    if (tile_outputs) *tile_outputs = info.tile_outputs;
+    if (pieces) *pieces = info.pieces;
+    return PCPP_OK;
 }
 
 PCPP_EXPORT int pcpp_conv3x3_export(const pcpp_conv_geom_t* g, const void* x, const void* row_up,
@@ -173,29 +217,7 @@ PCPP_EXPORT int pcpp_conv3x3_export(const pcpp_conv_geom_t* g, const void* x, co
         (bf16*)last_out);
     if (hipGetLastError() != hipSuccess) return PCPP_EHIP;
 
-    GemmParams p;
-    p.a = framed;
-    p.lda = 0;
-    p.a_f32 = 0;
-    p.w = (const __bf16*)w;
-    p.bias = (const __bf16*)bias;
-    p.M = g->batch * L.ho * L.wo;
-    p.N = g->c_out;
-    p.K = 9 * g->c_in;
-    p.geglu = 0;
-    p.F = 0;
-    p.resid = nullptr;
-    p.ldr = 0;
-    p.resid_f32 = 0;
-    p.out[0] = y;
-    p.out[1] = p.out[2] = nullptr;
-    p.seg = g->c_out;
-    p.ldo = g->c_out;
-    p.out_f32 = 0;
-    p.out_bf16 = nullptr;
-    p.conv_W = L.Wf;
-    p.conv_rows = L.Hf;
-    p.conv_stride = g->mode == PCPP_CONV_DOWN ? 2 : 1;
+    GemmParams p = conv_params(g, L, framed, w, bias, y);
     p.split_ws = split_ws;
     p.split_ws_bytes = L.split_bytes;
     return launch_gemm(p, s) == hipSuccess ? PCPP_OK : PCPP_EHIP;

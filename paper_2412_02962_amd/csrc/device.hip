@@ -64,6 +64,12 @@ DeviceLayout device_layout(hipStream_t stream) {
     return layout_for(cus, stream_cus(stream, cus));
 }
 
+bool layout_of_query(int cus, int cus_enabled, hipStream_t stream, DeviceLayout* d) {
+    if (cus < 0 || (cus > 0 && cus_enabled < 0)) return false;
+    *d = cus > 0 ? layout_for(cus, cus_enabled) : device_layout(stream);
+    return cus > 0 || device_cus() > 0;
+}
+
 // Workspace sizing: every compute unit usable; an MI355X's 256 when the
 // device cannot be asked (sizes are then upper bounds for that device).
 DeviceLayout device_layout_unmasked() {

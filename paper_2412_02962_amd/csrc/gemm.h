@@ -86,8 +86,18 @@ bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& us, int& shape);
 size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl);
 hipError_t launch_gemm_wide(const GemmParams& p, int shape, hipStream_t s);
 
+// Tokens and outputs of a tile of wide shape `shape`.
+void wide_tile(int shape, bool geglu, int32_t& tokens, int32_t& outputs);
+
 bool gemm_shape_ok(const GemmParams& p);
 hipError_t launch_gemm(const GemmParams& p, hipStream_t s);
+// What launch_gemm runs p on with layout `dl` and all the split workspace it
+// can use: tokens and outputs of a tile, pieces of K.  Launches nothing and
+// reads none of p's pointers.
+struct GemmPlanInfo {
+    int32_t tile_tokens, tile_outputs, pieces;
+};
+hipError_t gemm_plan_info(GemmParams p, const DeviceLayout& dl, GemmPlanInfo* info);
 // Two independent products (neither reads what the other writes) in one
 // launch when both run on the same pipelined kernel, else one after the other.
 hipError_t launch_gemm_pair(const GemmParams& a, const GemmParams& b, hipStream_t s);

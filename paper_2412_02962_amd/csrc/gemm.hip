@@ -1132,8 +1132,7 @@ struct GemmPlan {
     double us;  // estimated
 };
 
-hipError_t plan_gemm(GemmParams& p, hipStream_t s, GemmPlan& pl) {
-    const DeviceLayout dl = device_layout(s);
+hipError_t plan_gemm(GemmParams& p, const DeviceLayout& dl, GemmPlan& pl) {
     const GemmParams in = p;
     const hipError_t e = plan_narrow(p, dl, pl.kind);
     if (e != hipSuccess) return e;
@@ -1183,16 +1182,39 @@ void dma64_grid(const GemmParams& p, int& gx, int& gy) {
 hipError_t launch_gemm(const GemmParams& p_in, hipStream_t s) {
     GemmParams p = p_in;
     GemmPlan pl;
-    const hipError_t e = plan_gemm(p, s, pl);
+    const hipError_t e = plan_gemm(p, device_layout(s), pl);
     return e != hipSuccess ? e : launch_planned(p, pl, s);
+}
+
+hipError_t gemm_plan_info(GemmParams p, const DeviceLayout& dl, GemmPlanInfo* info) {
+    alignas(16) static char any[16];
+    p.split_ws = any;  // only looked at for its alignment
+    p.split_ws_bytes = SIZE_MAX;
+    GemmPlan pl;
+    const hipError_t e = plan_gemm(p, dl, pl);
+    if (e != hipSuccess) return e;
+    info->pieces = p.splitk;
+    switch (pl.kind) {
+        case GK_WIDE: wide_tile(pl.shape, p.geglu != 0, info->tile_tokens, info->tile_outputs); break;
+        case GK_DMA_64: info->tile_tokens = info->tile_outputs = 64; break;
+        case GK_G80:
+            info->tile_tokens = G80_BM;
+            info->tile_outputs = G80_BN;
+            break;
+        default:
+            info->tile_tokens = pl.kind == GK_REG_22 ? 128 : 64;
+            info->tile_outputs = pl.kind == GK_REG_11 || p.geglu ? 64 : 128;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipStream_t s) {
     GemmParams a = a_in, b = b_in;
     GemmPlan pa, pb;
-    hipError_t e = plan_gemm(a, s, pa);
+    const DeviceLayout dl = device_layout(s);
+    hipError_t e = plan_gemm(a, dl, pa);
     if (e != hipSuccess) return e;
-    e = plan_gemm(b, s, pb);
+    e = plan_gemm(b, dl, pb);
     if (e != hipSuccess) return e;
     // One launch on the 64 x 64 pipelined kernel where that is estimated to
     // be faster than the two planned ones: its workgroups share the compute
@@ -1200,7 +1222,6 @@ hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipS
     // the two blocks' text K/V: 11 us against 8 + 10).  Neither carries the
     // cross-attention epilogue, and at most one splits K (the split region
     // holds one product's partials).
-    const DeviceLayout dl = device_layout(s);
     GemmParams a64 = a;
     const bool plain_a = !a.a_f32 && !a.geglu && a.conv_W == 0 && a.K % DBK == 0 && a.N % 64 == 0 && a.seg % 4 == 0 &&
                          a.xa_T == 0;

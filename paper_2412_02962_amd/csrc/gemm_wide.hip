@@ -544,7 +544,26 @@ Choice choose(int M, int outs, int K, bool geglu, int seg, int w_seg_rows, size_
     return best;
 }
 
+// Bound on the byte offsets of the largest tile's rows of X from its first
+// row.  Convolution: 256 tokens reach (255 / wo + 1) output rows further,
+// each `stride` framed rows, and two framed rows more per image boundary;
+// one row for the place within a row.  (A bound that gives every token a row
+// of its own refuses the 3840 px ResNets: 1920 -> 640 on 60 rows of 240 columns
+// 885 us on 64 x 64 and 128 x 128 tiles, 541 on these; 960 -> 320 on 60 rows of
+// 480: 683 and 331.)
+int64_t x_span(const GemmParams& p) {
+    if (p.conv_W <= 0) return (int64_t)256 * p.lda * 2;
+    const int64_t wo = p.conv_W / p.conv_stride, per = (p.conv_rows / p.conv_stride) * wo;
+    const int64_t rows = (255 / wo + 1) * p.conv_stride + (255 / per + 1) * 2 + 1;
+    return rows * (p.conv_W + 2) * (p.K / 9) * 2;
+}
+
 }  // namespace
+
+void wide_tile(int shape, bool geglu, int32_t& tokens, int32_t& outputs) {
+    tokens = kShapes[shape].bm;
+    outputs = geglu ? kShapes[shape].bn / 2 : kShapes[shape].bn;
+}
 
 size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl) {
     if (M < 1 || N < 1 || K % KT != 0) return 0;
@@ -560,9 +579,7 @@ bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& limit_us, int& sha
         return false;
     // 32-bit offsets within a tile's rows of W and X
     const int64_t w_span = ((p.geglu ? (int64_t)p.F : 0) + 160) * p.K * 2;
-    const int64_t x_span = p.conv_W > 0 ? ((int64_t)256 * p.conv_stride + 2) * 9 * (p.conv_W + 2) * (p.K / 9) * 2
-                                        : (int64_t)256 * p.lda * 2;
-    if (w_span >= INT32_MAX || x_span >= INT32_MAX) return false;
+    if (w_span >= INT32_MAX || x_span(p) >= INT32_MAX) return false;
     const bool ws_ok = p.split_ws != nullptr && ((uintptr_t)p.split_ws & 15u) == 0;
     const Choice c = choose(p.M, p.N, p.K, p.geglu != 0, p.seg, p.w_seg_rows, ws_ok ? p.split_ws_bytes : 0, dl);
     if (c.shape < 0 || c.us >= limit_us) return false;

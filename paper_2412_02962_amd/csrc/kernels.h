@@ -47,6 +47,10 @@ DeviceLayout layout_for(int cus, int cus_enabled);  // pure: for planning and te
 int device_cus();                                    // current device, cached per device; 0 if unknown
 DeviceLayout device_layout(hipStream_t stream);      // current device, the stream's CU mask
 DeviceLayout device_layout_unmasked();               // current device, every compute unit (workspace sizing)
+// Layout that a plan query asks about: cus > 0 compute units of which
+// cus_enabled are usable, or (cus = 0) the current device and the stream's CU
+// mask.  False for invalid counts or a device that cannot be asked.
+bool layout_of_query(int cus, int cus_enabled, hipStream_t stream, DeviceLayout* d);
 
 // bf16 path: workspace bytes it needs (work counters and float32 partial
 // results of query blocks split across workgroups; sized for a launch that

@@ -203,14 +203,8 @@ PCPP_EXPORT int pcpp_partial_attention_plan(const pcpp_geom_t* g, int32_t cus, i
     int st = validate_geom(g, &r);
     if (st != PCPP_OK) return st;
     if (g->dtype != PCPP_DTYPE_BF16 || g->head_dim != 64) return PCPP_ENOTSUP;
-    if (cus < 0 || (cus > 0 && cus_enabled < 0)) return PCPP_EINVAL;
     DeviceLayout d;
-    if (cus > 0) {
-        d = layout_for(cus, cus_enabled);
-    } else {
-        d = device_layout((hipStream_t)stream);
-        if (device_cus() <= 0) return PCPP_EHIP;
-    }
+    if (!layout_of_query(cus, cus_enabled, (hipStream_t)stream, &d)) return cus == 0 ? PCPP_EHIP : PCPP_EINVAL;
     KvSource kv = make_kv_source(g, r, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     const AttnPlanInfo pi = attention_bf16_plan(make_attn_params(g, r, nullptr, nullptr, kv), d);
     if (block_queries) *block_queries = pi.block_queries;

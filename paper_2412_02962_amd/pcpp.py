@@ -164,6 +164,7 @@ def _load():
         "pcpp_conv3x3_workspace_size": (sz, [ctypes.POINTER(pcpp_conv_geom_t)]),
         "pcpp_conv3x3": (ctypes.c_int, [ctypes.POINTER(pcpp_conv_geom_t)] + [vp] * 7 + [sz, vp]),
         "pcpp_conv3x3_export": (ctypes.c_int, [ctypes.POINTER(pcpp_conv_geom_t)] + [vp] * 9 + [sz, vp]),
+        "pcpp_conv3x3_plan": (ctypes.c_int, [ctypes.POINTER(pcpp_conv_geom_t), i32, i32, vp, i32p, i32p, i32p]),
     }
     for name, (res, args) in sig.items():
         f = getattr(lib, name)
@@ -182,7 +183,7 @@ EXPORTED = (
     "pcpp_partial_attention_multihop_workspace_size", "pcpp_partial_attention_multihop",
     "pcpp_multihop_message_bytes", "pcpp_pack_multihop", "pcpp_unpack_multihop",
     "pcpp_resnet_block_workspace_size", "pcpp_resnet_block", "pcpp_guided_step",
-    "pcpp_conv3x3_workspace_size", "pcpp_conv3x3", "pcpp_conv3x3_export",
+    "pcpp_conv3x3_workspace_size", "pcpp_conv3x3", "pcpp_conv3x3_export", "pcpp_conv3x3_plan",
     "pcpp_transformer_module_workspace_size", "pcpp_transformer_module",
     "pcpp_concat_channels", "pcpp_layer_norm", "pcpp_group_norm_workspace_size", "pcpp_group_norm",
 )
@@ -402,6 +403,17 @@ def pcpp_conv3x3_export(g, x, row_up, row_dn, w, bias, y, first_out, last_out, w
     _check("pcpp_conv3x3_export", _lib.pcpp_conv3x3_export(
         ctypes.byref(g), _ptr(x), _ptr(row_up), _ptr(row_dn), _ptr(w), _ptr(bias), _ptr(y), _ptr(first_out),
         _ptr(last_out), _ptr(workspace), ws_bytes, _stream(stream)))
+
+
+def pcpp_conv3x3_plan(g, cus=0, cus_enabled=0, stream=None):
+    """(tokens, outputs, pieces of k) of the convolution's tiles: on a device of
+    `cus` compute units with `cus_enabled` usable, or (cus = 0) on the current
+    device with the CU mask of `stream`."""
+    bm, bn, k = (ctypes.c_int32() for _ in range(3))
+    st = _stream(stream) if cus == 0 else None
+    _check("pcpp_conv3x3_plan", _lib.pcpp_conv3x3_plan(
+        ctypes.byref(g), cus, cus_enabled, st, ctypes.byref(bm), ctypes.byref(bn), ctypes.byref(k)))
+    return bm.value, bn.value, k.value
 
 
 def make_module_weights(module: dict, blocks: list, ff_inner: int, gn_groups: int):

@@ -36,6 +36,20 @@ def test_wide_convolution(case):
     conv._check(got, want, str(case))
 
 
+# rows so wide that a tile spans a few of them (3840 px images): (tokens,
+# outputs, pieces) with a ragged last tile
+@pytest.mark.parametrize("case,plan", [((36, 240, 6, 2, 1920, 640, 1, 0), (128, 128, 4)),
+                                       ((27, 480, 9, 1, 960, 320, 1, 0), (128, 160, 8)),
+                                       ((10, 480, 5, 4, 1920, 640, 1, 1), (128, 128, 8))],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_wide_images(case, plan):
+    from paper_2412_02962_amd import pcpp
+    conv._say("wide image", case, plan)
+    assert pcpp.pcpp_conv3x3_plan(pcpp.make_conv_geom(*case)) == plan
+    got, want = conv._run(*case, seed=110)
+    conv._check(got, want, str(case))
+
+
 def test_split_pieces_give_the_same_bits_again():
     """The pieces of a tile are added in order, whichever arrives last."""
     case = CASES[1]
