@@ -130,7 +130,9 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnParams p) {
         const double mx = fmax(fmax(s[0], s[1]), fmax(s[2], s[3]));
         if (__any(mx > m_run + LIMIT)) {
             const double m_new = fmax(m_run, xor_max(xor_max(mx, 16), 32));
-            const double alpha = exp(m_run - m_new);
+            // (equal: also a query whose scores so far are all -inf, where the
+            // difference is no number)
+            const double alpha = m_new == m_run ? 1.0 : exp(m_run - m_new);
             m_run = m_new;
             l_run *= alpha;
 #pragma unroll

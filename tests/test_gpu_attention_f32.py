@@ -62,3 +62,24 @@ def test_f32_value_rows_past_the_end_weigh_nothing():
     out = gu.to_f64(gu.run_attention(cfg, inp)).reshape(cfg.n_q, cfg.C)
     assert np.isposinf(out[:, 5]).all()
     assert np.isfinite(np.delete(out, 5, axis=1)).all()
+
+
+# keys whose scores are -inf for half of the queries (and +inf, so no number,
+# for the others, which share their workgroups): the first tile of the second
+# wavefront's keys, all of its keys, tiles in the middle of a wavefront's
+@pytest.mark.parametrize("first,last", [(64, 80), (64, 128), (144, 176)])
+def test_f32_scores_of_minus_infinity(first, last):
+    """Keys of weight 0 leave the other keys' share as it is."""
+    cfg = _cfg(16, 16, 1, 0, 0.0, 2)
+    inp = {k: (None if v is None else v.copy()) for k, v in synth.attention_inputs(cfg).items()}
+    inp["k_fresh"][:, first:last, ::64] = np.inf        # dimension 0 of each head
+    finite = inp["q"][..., ::64] < 0                    # [batch, query, head]
+    assert finite.any() and not finite.all()
+    got = gu.to_f64(gu.run_attention(cfg, inp)).reshape(cfg.n_q, cfg.heads, 64)
+    with np.errstate(invalid="ignore"):
+        want = gu.oracle_attention(cfg, inp).reshape(got.shape)
+    finite = finite.reshape(cfg.n_q, cfg.heads)
+    assert np.isfinite(want[finite]).all() and np.isnan(want[~finite]).all()
+    assert np.isnan(got[~finite]).all() and np.isfinite(got[finite]).all()
+    # the bound of _check
+    assert (np.abs(got - want)[finite] <= 2.0 ** -23 * np.abs(want[finite]) + 1e-9).all()
