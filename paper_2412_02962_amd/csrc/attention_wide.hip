@@ -249,14 +249,16 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_wide_kernel(AttnParams p, Sc
                 m4[i] = fmaxf(fmaxf(s[A][4 * i], s[A][4 * i + 1]), fmaxf(s[A][4 * i + 2], s[A][4 * i + 3]));
             const float mx = max_xor32(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]))) * sl2;
             const float m_new = fmaxf(m_run[A], mx);
-            const float alpha = fast_exp2(m_run[A] - m_new);
+            // A query whose scores so far are all -inf: the maxima are equal and
+            // their difference no number; its probabilities are exp2(-inf) = 0.
+            const float alpha = m_new == m_run[A] ? 1.f : fast_exp2(m_run[A] - m_new);
             m_run[A] = m_new;
             l_run[A] *= alpha;
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[A][mb][r] *= alpha;
-            mneg = -m_new;
+            mneg = m_new == -INFINITY ? 0.f : -m_new;
 #pragma unroll
             for (int i = 0; i < 8; ++i) pair(i);
             lt = acc0;
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_wide_kernel(AttnParams p, Sc
     };
     if (sc.k == 1) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) store_out(u, o[u], l_tot[u] > 0.f ? 1.0f / l_tot[u] : 0.f);
+        for (int u = 0; u < 2; ++u) store_out(u, o[u], 1.0f / l_tot[u]);
         return;
     }
     auto part_of = [&](int w, int u) INLINE {
@@ -390,8 +392,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_wide_kernel(AttnParams p, Sc
         };
         auto combine = [&](const f32x4 (&pc)[8], float mk, float lk) {
             const float Mn = fmaxf(M, mk);
-            const float a = fast_exp2(M - Mn);
-            const float w = fast_exp2(mk - Mn);
+            const float a = M == Mn ? 1.f : fast_exp2(M - Mn);  // (both may be -inf)
+            const float w = mk == Mn ? 1.f : fast_exp2(mk - Mn);
             L = __builtin_fmaf(lk, w, L * a);
 #pragma unroll
             for (int c = 0; c < 8; ++c)
@@ -413,7 +415,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void attn_wide_kernel(AttnParams p, Sc
                 combine(pc_b, m_b, l_b);
             }
         }
-        store_out(u, res, L > 0.f ? 1.0f / L : 0.f);
+        store_out(u, res, 1.0f / L);
     }
 }
 
