@@ -40,10 +40,10 @@ __host__ __device__ inline int gn_group_lanes(int G) {
 // Statistics of image b for the calling workgroup (its first 256 threads do
 // the work; all must call): S consecutive lanes per group merge chunks j, j +
 // S, ... each and meet in a shuffle tree; the bands' statistics, a lane each
-// and loaded before everything else (a chain of eight dependent loads took 4
-// us), are then merged in band order by the group's first lane.  Writes
-// g_mean[G] and g_rstd[G] (LDS) and the band's own statistics if write_own;
-// ends with a workgroup barrier.
+// and loaded before everything else, up to 2 S of them (a chain of eight
+// dependent loads took 4 us), are then merged in band order by the group's
+// first lane.  Writes g_mean[G] and g_rstd[G] (LDS) and the band's own
+// statistics if write_own; ends with a workgroup barrier.
 __device__ __forceinline__ void gn_group_stats(const GnStatsSrc& a, int b, bool write_own, float* g_mean,
                                                float* g_rstd) {
     const int tid = threadIdx.x;
@@ -52,14 +52,20 @@ __device__ __forceinline__ void gn_group_stats(const GnStatsSrc& a, int b, bool 
         const int S = gn_group_lanes(G);
         const int g = min(tid / S, G - 1), j = tid % S;
         const bool mine = tid / S < G;
-        float bn = 0.f, bm = 0.f, bq = 0.f;  // band j's statistics
-        auto load_band = [&](int jb) {
-            const float* o = a.bands + (((int64_t)min(jb, a.n_bands - 1) * a.B + b) * G + g) * 3;
-            bn = o[0];
-            bm = o[1];
-            bq = o[2];
+        struct Band {
+            float n, mean, m2;
         };
-        if (a.bands != nullptr) load_band(j);
+        Band cur = {}, next = {};  // this lane's of S bands, and of the S after them
+        auto load_band = [&](int jb, Band& x) {
+            const float* o = a.bands + (((int64_t)min(jb, a.n_bands - 1) * a.B + b) * G + g) * 3;
+            x.n = o[0];
+            x.mean = o[1];
+            x.m2 = o[2];
+        };
+        if (a.bands != nullptr) {
+            load_band(j, cur);
+            load_band(S + j, next);
+        }
         float n = 0.f, mean = 0.f, m2 = 0.f;
         const float* st = a.stats + ((int64_t)b * a.chunks * G + g) * 3;
         for (int k0 = j; k0 < a.chunks; k0 += 4 * S) {
@@ -96,9 +102,13 @@ __device__ __forceinline__ void gn_group_stats(const GnStatsSrc& a, int b, bool 
             const int lane0 = (tid & 63) - j;
             float tn = 0.f, tm = 0.f, tq = 0.f;
             for (int jb = 0; jb < a.n_bands; ++jb) {
-                if (jb > 0 && jb % S == 0) load_band(jb + j);
-                const float on = __shfl(bn, lane0 + jb % S), om = __shfl(bm, lane0 + jb % S),
-                            oq = __shfl(bq, lane0 + jb % S);
+                const int at = jb & (S - 1);
+                if (jb > 0 && at == 0) {
+                    cur = next;
+                    if (jb + S < a.n_bands) load_band(jb + S + j, next);
+                }
+                const float on = __shfl(cur.n, lane0 + at), om = __shfl(cur.mean, lane0 + at),
+                            oq = __shfl(cur.m2, lane0 + at);
                 if (jb == a.band)
                     chan_merge(tn, tm, tq, n, mean, m2);
                 else

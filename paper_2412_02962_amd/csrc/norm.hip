@@ -45,6 +45,30 @@ __host__ __device__ inline int gn_chunk_tokens(int N) { return N >= 64 * GN_CHUN
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
+// Sum over T consecutive lanes (a power of two up to a wavefront, at a
+// multiple of T), the same bits in each of them: quad permutes, the half-row
+// and row mirrors (DPP), then the 16- and 32-lane swaps; no LDS round trip.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lanes_sum(float v, int T) {
+    if (T >= 2) v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    if (T >= 4) v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    if (T >= 8) v = dpp_add<0x141>(v);  // row_half_mirror
+    if (T >= 16) v = dpp_add<0x140>(v);  // row_mirror
+    if (T >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if (T >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    return v;
+}
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum(v, 64); }
+
 // Workspace of GroupNorm: [B][chunks][G] x (count, mean, M2).
 size_t gn_part_bytes(int B, int G, int chunks) { return (size_t)B * G * chunks * 3 * sizeof(float); }
 
@@ -142,94 +166,119 @@ __global__ __launch_bounds__(GN_THREADS) void gn_stats_rows(GroupNormParams p) {
     }
 }
 
-// Statistics of a chunk of tokens and a slab of S channels (whole groups,
-// whole 16-byte vectors): a thread holds one vector of up to KR rows in
-// registers.  Splitting the channels as well keeps the launch at about one
-// workgroup per compute unit with 16 (32) chunks per image, whose records
-// every consumer merges: with 64 to 256 chunks the merge was most of the
-// apply's time (statistics and apply of 2 x 8192 x 960: 10 + 35 us, now 11 +
-// 22; of 2 x 8192 x 320: 5 + 26, now 8 + 13; of 2048 x 640: 6.6 + 9.8, now 6.1
-// + 7.4).  Sums: over a thread's rows, over the threads of a channel
-// (LDS), over the channels of a group (one wavefront each).
+// A slab launch: slabs of S channels (gs whole groups of cg, V whole 16-byte
+// vectors) and chunks of ct tokens.  RP rows of the slab fit the workgroup
+// side by side; T = 2^log_T lanes sum a group.  The kernel divides by cg and V through
+// their inverses (ceil(2^16 / x), exact for the dividends below 256 that it
+// has): a division by a kernel argument is 30 instructions.
+struct Slab {
+    int32_t S, ct, cg, gs, V, RP, log_T, inv_cg, inv_V;
+};
+
+// Statistics of a chunk of tokens and a slab of channels: a thread holds one
+// vector of up to KR rows in registers.  Splitting the channels as well keeps
+// the launch at about one workgroup per compute unit with 16 (32) chunks per
+// image, whose records every consumer merges: with 64 to 256 chunks the merge
+// was most of the apply's time (statistics and apply of 2 x 8192 x 960: 9.6 +
+// 27.7 us, now 9.2 + 18.6; of 2 x 8192 x 320: 5.7 + 21.4, now 5.6 + 8.8; of 2048
+// x 640: 6.9 + 6.7, now 4.8 + 5.7).  A small band's launch is the chain of one
+// workgroup: the load, two sums over a thread's rows, the threads of a group
+// (LDS) and the group's lanes (DPP), three barriers: 512 x 1280 4.5 us, 2 x
+// 133 x 64 with 64 groups 3.7 (gn_stats_rows 5.2 and 3.6; with a sum over the
+// threads of a channel first, LDS permutes and a division per channel 5.9
+// and 14).
 template <int KR>
-__global__ __launch_bounds__(GN_THREADS) void gn_stats_slab(GroupNormParams p, int S, int ct) {
-    __shared__ __attribute__((aligned(16))) float part[GN_THREADS * 8];
-    __shared__ float chan[GN_THREADS];
-    __shared__ float total[GN_THREADS];  // per group of the slab
+__global__ __launch_bounds__(GN_THREADS) void gn_stats_slab(GroupNormParams p, Slab a) {
+    __shared__ __attribute__((aligned(16))) float part[GN_THREADS * 8];  // [row of RP][channel of the slab]
+    __shared__ float g_mean[GN_THREADS];
     const int ch = blockIdx.x, b = blockIdx.z;
     const int tid = threadIdx.x;
+    const int r0 = (tid * a.inv_V) >> 16, v = tid - r0 * a.V;
+    const int t0 = ch * a.ct, nt = min(a.ct, p.N - t0);
+    const bf16* xb = p.x + ((int64_t)b * p.N + t0) * p.C + blockIdx.y * a.S + 8 * v;
+    bf16x8 x[KR];
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+        const int r = r0 + k * a.RP;
+        x[k] = bf16x8{};
+        if (r0 < a.RP && r < nt) x[k] = *(const bf16x8*)(xb + (int64_t)r * p.C);
+    }
     if (ch == 0 && blockIdx.y == 0 && b == 0) {
         if (p.zero != nullptr)
             for (int i = tid; i < p.n_zero; i += GN_THREADS) p.zero[i] = 0;
         if (p.zero2 != nullptr)
             for (int i = tid; i < p.n_zero2; i += GN_THREADS) p.zero2[i] = 0;
     }
-    const int cg = p.C / p.G, gs = S / cg, V = S / 8, RP = GN_THREADS / V, QN = GN_THREADS / S;
-    const int v = tid % V, r0 = tid / V;
-    const int t0 = ch * ct, nt = min(ct, p.N - t0);
-    const bf16* xb = p.x + ((int64_t)b * p.N + t0) * p.C + blockIdx.y * S + 8 * v;
-    bf16x8 x[KR];
+    // Lanes u = 0 .. T - 1 of group g add every T-th of its values in part,
+    // row by row, and then theirs.
+    const int T = 1 << a.log_T, g = tid >> a.log_T, u = tid & (T - 1);
+    const int u_r = (u * a.inv_cg) >> 16, u_c = u - u_r * a.cg;
+    const int step_r = (T * a.inv_cg) >> 16, step_c = T - step_r * a.cg;
+    const int step_at = step_r * a.S + step_c;
+    const int rows = min(a.RP, nt);  // (the others are zeros)
+    const int n_sum = (rows * a.cg + T - 1) >> a.log_T;
+    auto group_sum = [&](const float (&s)[8]) {
+        if (r0 < a.RP) {
+            *(f32x4*)(part + r0 * a.S + 8 * v) = f32x4{s[0], s[1], s[2], s[3]};
+            *(f32x4*)(part + r0 * a.S + 8 * v + 4) = f32x4{s[4], s[5], s[6], s[7]};
+        }
+        __syncthreads();
+        float sum = 0.f;
+        int r = g < a.gs ? u_r : rows, c = u_c, at = g * a.cg + u_r * a.S + u_c;
+        for (int k = 0; k < n_sum; k += 4) {  // four reads in flight
+            float w[4];
 #pragma unroll
-    for (int k = 0; k < KR; ++k) {
-        const int r = r0 + k * RP;
-        x[k] = bf16x8{};
-        if (r0 < RP && r < nt) x[k] = *(const bf16x8*)(xb + (int64_t)r * p.C);
-    }
-    // Group sums of s (a thread's sums of its eight channels) into total[].
-    auto reduce = [&](const float (&s)[8]) {
-        if (r0 < RP) {
-            *(f32x4*)(part + r0 * S + 8 * v) = f32x4{s[0], s[1], s[2], s[3]};
-            *(f32x4*)(part + r0 * S + 8 * v + 4) = f32x4{s[4], s[5], s[6], s[7]};
+            for (int j = 0; j < 4; ++j) {
+                w[j] = part[r < rows ? at : 0];
+                if (r >= rows) w[j] = 0.f;
+                const bool wrap = c + step_c >= a.cg;
+                c += wrap ? step_c - a.cg : step_c;
+                r += wrap ? step_r + 1 : step_r;
+                at += step_at + (wrap ? a.S - a.cg : 0);
+            }
+            sum += (w[0] + w[1]) + (w[2] + w[3]);
         }
-        __syncthreads();
-        const int c = tid % S, q = tid / S;
-        if (q < QN) {
-            float a = 0.f;
-            for (int r = q; r < RP; r += QN) a += part[r * S + c];
-            chan[q * S + c] = a;
-        }
-        __syncthreads();
-        const int lane = tid & 63;
-        for (int g = tid >> 6; g < gs; g += GN_THREADS / 64) {
-            float a = 0.f;
-            for (int q2 = 0; q2 < QN; ++q2)
-                for (int c2 = lane; c2 < cg; c2 += 64) a += chan[q2 * S + g * cg + c2];
-            for (int o = 1; o < 64; o <<= 1) a += __shfl_xor(a, o);
-            if (lane == 0) total[g] = a;
-        }
-        __syncthreads();
+        return lanes_sum(sum, T);
     };
-    const float n_chunk = (float)nt * (float)cg;
+    const float n_chunk = (float)nt * (float)a.cg;
     float s[8] = {};
 #pragma unroll
     for (int k = 0; k < KR; ++k)
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[e] += (float)x[k][e];  // rows past the end are zeros
-    reduce(s);
+    const float mean_g = group_sum(s) / n_chunk;
+    if (g < a.gs && u == 0) g_mean[g] = mean_g;
+    __syncthreads();
     // Second pass: squared deviations from the chunk mean of the channel's group.
     float mean[8];
+    {
+        int ge = (8 * v * a.inv_cg) >> 16, left = (ge + 1) * a.cg - 8 * v;  // channels left in group ge
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        mean[e] = total[(8 * v + e) / cg] / n_chunk;
-        s[e] = 0.f;
+        for (int e = 0; e < 8; ++e) {
+            if (left == 0) {
+                ++ge;
+                left = a.cg;
+            }
+            --left;
+            mean[e] = g_mean[ge];
+            s[e] = 0.f;
+        }
     }
-    float own_mean = 0.f;
-    if (tid < gs) own_mean = total[tid] / n_chunk;
 #pragma unroll
     for (int k = 0; k < KR; ++k)
-        if (r0 + k * RP < nt) {
+        if (r0 + k * a.RP < nt) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float d = (float)x[k][e] - mean[e];
                 s[e] += d * d;
             }
         }
-    reduce(s);
-    if (tid < gs) {
-        float* st = p.stats + (((int64_t)b * p.chunks + ch) * p.G + blockIdx.y * gs + tid) * 3;
+    const float m2 = group_sum(s);
+    if (g < a.gs && u == 0) {
+        float* st = p.stats + (((int64_t)b * p.chunks + ch) * p.G + blockIdx.y * a.gs + g) * 3;
         st[0] = n_chunk;
-        st[1] = own_mean;
-        st[2] = total[tid];
+        st[1] = mean_g;
+        st[2] = m2;
     }
 }
 
@@ -348,24 +397,6 @@ __global__ __launch_bounds__(GA_THREADS) void gn_apply(GroupNormParams p) {
 
 constexpr int LN_MAX_VEC = 8;  // 16-byte fp32 vectors per lane: C <= 2048
 
-// Sum over the 64 lanes of a wavefront, the same bits in every lane:
-// quad permutes, the half-row and row mirrors (DPP), then the 16- and
-// 32-lane swaps; no LDS round trip.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_sum(float v) {
-    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    v = dpp_add<0x141>(v);  // row_half_mirror
-    v = dpp_add<0x140>(v);  // row_mirror
-    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
-    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
-}
-
 template <int NV>  // 16-byte vectors per lane: C <= 256 * NV
 __global__ __launch_bounds__(256) void ln_kernel(LayerNormParams p) {
     const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -427,18 +458,18 @@ int gn_chunks(int N) {
     return N > 0 ? (N + ct - 1) / ct : 1;
 }
 
-// Slab of channels and tokens per chunk of gn_stats_slab; S = 0 where the
-// groups do not fit it (a multiple of whole groups and of 8 channels above
-// 256).  16 chunks per image (32 from 4096 tokens on), more where a thread
-// would hold over 16 rows; the widest slab that still gives a workgroup per
-// compute unit.
+// Plan of gn_stats_slab; S = 0 where the groups do not fit it (a multiple of
+// whole groups and of 8 channels above 256).  16 chunks per image (32 from
+// 4096 tokens on), more where a thread would hold over 16 rows; the widest
+// slab that still gives a workgroup per compute unit.
 struct SlabPlan {
-    int S, ct, chunks, rows;  // rows: per thread
+    Slab a;
+    int chunks, rows;  // rows: per thread
 };
 constexpr int GN_SLAB_ROWS = 16;
 
 SlabPlan slab_plan(int B, int N, int C, int G, int cus) {
-    SlabPlan sp{0, 0, 0, 0};
+    SlabPlan sp{};
     const int cg = C / G;
     int unit = cg;
     while (unit % 8 != 0) unit += cg;  // C is a multiple of 8 and of cg: so is this of C
@@ -448,14 +479,21 @@ SlabPlan slab_plan(int B, int N, int C, int G, int cus) {
     int S = unit;
     for (int s = unit; s <= GN_THREADS; s += unit)
         if (C % s == 0 && (int64_t)chunks * B * (C / s) >= cus) S = s;
-    const int rp = GN_THREADS / (S / 8);
-    int ct = (N + chunks - 1) / chunks;
-    if (ct > GN_SLAB_ROWS * rp) ct = GN_SLAB_ROWS * rp;
-    sp.chunks = (N + ct - 1) / ct;
+    Slab a{};
+    a.V = S / 8;
+    a.RP = GN_THREADS / a.V;
+    a.ct = (N + chunks - 1) / chunks;
+    if (a.ct > GN_SLAB_ROWS * a.RP) a.ct = GN_SLAB_ROWS * a.RP;
+    sp.chunks = (N + a.ct - 1) / a.ct;
     if (sp.chunks > gn_chunks(N)) return sp;
-    sp.S = S;
-    sp.ct = ct;
-    sp.rows = (ct + rp - 1) / rp;
+    a.S = S;
+    a.cg = cg;
+    a.gs = S / cg;
+    while ((1 << a.log_T) < gn_group_lanes(a.gs)) ++a.log_T;
+    a.inv_cg = (65536 + cg - 1) / cg;
+    a.inv_V = (65536 + a.V - 1) / a.V;
+    sp.a = a;
+    sp.rows = (a.ct + a.RP - 1) / a.RP;
     return sp;
 }
 
@@ -473,17 +511,17 @@ static hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
     if (!gn_shapes_ok(p.C, p.G)) return hipErrorInvalidValue;
     if (p.pad_W < 0 || (p.pad_W > 0 && p.N % p.pad_W != 0)) return hipErrorInvalidValue;
     const SlabPlan sp = slab_plan(p.B, p.N, p.C, p.G, device_layout(s).cus);
-    if (sp.S > 0) {
+    if (sp.a.S > 0) {
         p.chunks = sp.chunks;
-        const dim3 grid((unsigned)sp.chunks, (unsigned)(p.C / sp.S), (unsigned)p.B);
+        const dim3 grid((unsigned)sp.chunks, (unsigned)(p.C / sp.a.S), (unsigned)p.B);
         if (sp.rows <= 2)
-            gn_stats_slab<2><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+            gn_stats_slab<2><<<grid, GN_THREADS, 0, s>>>(p, sp.a);
         else if (sp.rows <= 4)
-            gn_stats_slab<4><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+            gn_stats_slab<4><<<grid, GN_THREADS, 0, s>>>(p, sp.a);
         else if (sp.rows <= 8)
-            gn_stats_slab<8><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+            gn_stats_slab<8><<<grid, GN_THREADS, 0, s>>>(p, sp.a);
         else
-            gn_stats_slab<GN_SLAB_ROWS><<<grid, GN_THREADS, 0, s>>>(p, sp.S, sp.ct);
+            gn_stats_slab<GN_SLAB_ROWS><<<grid, GN_THREADS, 0, s>>>(p, sp.a);
         return hipGetLastError();
     }
     p.chunks = gn_chunks(p.N);
