@@ -277,6 +277,16 @@ size_t pcpp_transformer_block_workspace_size(const pcpp_geom_t* g,
                                              int32_t n_text, int32_t text_dim);
 
 /*
+ * Launch plan of a block's GEGLU product on g's tokens, heads * 64 channels
+ * and ff_inner outputs (host only, no GPU work; for diagnostics and tests);
+ * cus, cus_enabled and stream as for pcpp_partial_attention_plan.  Outputs
+ * (any may be NULL): tokens and outputs of a workgroup's tile, and how many
+ * workgroups share a compute unit.
+ */
+int pcpp_geglu_plan(const pcpp_geom_t* g, int32_t ff_inner, int32_t cus, int32_t cus_enabled,
+                    void* stream, int32_t* tile_tokens, int32_t* tile_outputs, int32_t* per_cu);
+
+/*
  * One SDXL-shaped transformer block on band i, bf16 storage with float32
  * accumulation (the method applies to the self-attention only, Sec. 3.3;
  * GroupNorm here uses the band's own statistics):

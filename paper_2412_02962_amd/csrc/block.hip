@@ -145,6 +145,14 @@ GemmParams gemm(const void* a, int64_t lda, bool a_f32, const void* wt, const vo
     return p;
 }
 
+// u [M, F] = value * GELU(gate), W rows 0 .. F - 1 the values, F .. 2 F - 1 the gates.
+GemmParams geglu(const void* a, const void* wt, const void* bias, int M, int F, int K, void* u) {
+    GemmParams p = gemm(a, K, false, wt, bias, M, F, K, u, F, false);
+    p.geglu = 1;
+    p.F = F;
+    return p;
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
@@ -393,10 +401,7 @@ int run_module(const pcpp_geom_t* g, const ModuleW& mw, const pcpp_basic_block_w
         lp.beta = (const __bf16*)w.ln3_beta;
         PCPP_CHECK(launch_layer_norm(lp, s));
         {
-            GemmParams ff = gemm(t16, C, false, w.ff1_w, w.ff1_b, rows, F, C, u16, F, false);
-            ff.geglu = 1;
-            ff.F = F;
-            PCPP_CHECK(gemm_s(ff));
+            PCPP_CHECK(gemm_s(geglu(t16, w.ff1_w, w.ff1_b, rows, F, C, u16)));
         }
         {
             GemmParams o = gemm(u16, F, false, w.ff2_w, w.ff2_b, rows, C, F, hid, C, true);
@@ -444,6 +449,22 @@ PCPP_EXPORT size_t pcpp_transformer_block_workspace_size(const pcpp_geom_t* g, c
     Geo r;
     if (w == nullptr || validate_block(g, w->ff_inner, w->gn_groups, n_text, text_dim, &r) != PCPP_OK) return 0;
     return layout(g, r, w->ff_inner, w->gn_groups, n_text, text_dim, 1).total;
+}
+
+PCPP_EXPORT int pcpp_geglu_plan(const pcpp_geom_t* g, int32_t ff_inner, int32_t cus, int32_t cus_enabled, void* stream,
+                                int32_t* tile_tokens, int32_t* tile_outputs, int32_t* per_cu) {
+    Geo r;
+    const int st = validate_block(g, ff_inner, 1, 1, 64, &r);
+    if (st != PCPP_OK) return st;
+    DeviceLayout d;
+    if (!layout_of_query(cus, cus_enabled, (hipStream_t)stream, &d)) return cus == 0 ? PCPP_EHIP : PCPP_EINVAL;
+    GemmPlanInfo info;
+    if (gemm_plan_info(geglu(nullptr, nullptr, nullptr, g->batch * r.nq, ff_inner, r.C, nullptr), d, &info) != hipSuccess)
+        return PCPP_ENOTSUP;
+    if (tile_tokens) *tile_tokens = info.tile_tokens;
+    if (tile_outputs) *tile_outputs = info.tile_outputs;
+    if (per_cu) *per_cu = info.per_cu;
+    return PCPP_OK;
 }
 
 PCPP_EXPORT int pcpp_transformer_block(const pcpp_geom_t* g, const pcpp_block_weights_t* w, const void* x,

@@ -86,16 +86,18 @@ bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& us, int& shape);
 size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl);
 hipError_t launch_gemm_wide(const GemmParams& p, int shape, hipStream_t s);
 
-// Tokens and outputs of a tile of wide shape `shape`.
-void wide_tile(int shape, bool geglu, int32_t& tokens, int32_t& outputs);
+// Tokens and outputs of a tile of wide shape `shape`, and how many of its
+// workgroups share a compute unit.
+void wide_tile(int shape, bool geglu, int32_t& tokens, int32_t& outputs, int32_t& per_cu);
 
 bool gemm_shape_ok(const GemmParams& p);
 hipError_t launch_gemm(const GemmParams& p, hipStream_t s);
 // What launch_gemm runs p on with layout `dl` and all the split workspace it
-// can use: tokens and outputs of a tile, pieces of K.  Launches nothing and
-// reads none of p's pointers.
+// can use: tokens and outputs of a tile, pieces of K, workgroups on a compute
+// unit (wide tiles only, else 0).  Launches nothing and reads none of p's
+// pointers.
 struct GemmPlanInfo {
-    int32_t tile_tokens, tile_outputs, pieces;
+    int32_t tile_tokens, tile_outputs, pieces, per_cu;
 };
 hipError_t gemm_plan_info(GemmParams p, const DeviceLayout& dl, GemmPlanInfo* info);
 // Two independent products (neither reads what the other writes) in one

@@ -1194,8 +1194,11 @@ hipError_t gemm_plan_info(GemmParams p, const DeviceLayout& dl, GemmPlanInfo* in
     const hipError_t e = plan_gemm(p, dl, pl);
     if (e != hipSuccess) return e;
     info->pieces = p.splitk;
+    info->per_cu = 0;
     switch (pl.kind) {
-        case GK_WIDE: wide_tile(pl.shape, p.geglu != 0, info->tile_tokens, info->tile_outputs); break;
+        case GK_WIDE:
+            wide_tile(pl.shape, p.geglu != 0, info->tile_tokens, info->tile_outputs, info->per_cu);
+            break;
         case GK_DMA_64: info->tile_tokens = info->tile_outputs = 64; break;
         case GK_G80:
             info->tile_tokens = G80_BM;

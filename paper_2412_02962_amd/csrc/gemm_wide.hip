@@ -489,10 +489,10 @@ hipError_t launch_shape(const GemmParams& p, hipStream_t s) {
 }
 
 // The tiles, with the measured microseconds of one round of workgroups: ends
-// (first loads, stores), per k-tile (with one workgroup on a compute unit,
-// and with `share`), and the merge of split pieces.
+// (first loads, stores), per k-tile (of a launch with at most one workgroup
+// per compute unit, and with more), and the merge of split pieces.
 struct Shape {
-    int bm, bn, share;
+    int bm, bn, share;  // share: workgroups on a compute unit
     double ends, ktile, ktile_shared, merge;
 };
 constexpr Shape kShapes[] = {
@@ -501,7 +501,22 @@ constexpr Shape kShapes[] = {
     {128, 128, 1, 4.0, 0.57, 0.57, 5.0},  // 128 KB, four stages
     {64, 128, 2, 3.3, 0.40, 0.77, 5.0},   // 72 KB, three stages, four wavefronts
 };
-constexpr double kLaunch = 4.0;
+// GEGLU, fitted to 100 products of 65 to 40000 tokens and K = 64 to 1280
+// (launch 2 us; the estimate's choice is on average 1 % over the fastest
+// tile). It never splits. Short K and several rounds of workgroups want
+// small tiles, whose ends hide behind other workgroups of the unit: with two
+// stages of 64 x 128 (48 KB) three of them share one. 2072 x 1280 x 320: 16.2 us
+// on 256 x 160, 12.4 there; 8219 x 1024 x 256: 30.4 on 128 x 128, 22.4; 23864 x
+// 2048 x 512: 206 and 155. (Plain products and convolutions keep the first
+// four: they have the 64 x 64 and 64 x 80 tiles of gemm.hip beside them.)
+constexpr Shape kGegluShapes[] = {
+    {256, 160, 1, 7.5, 0.92, 1.12, 0.0},
+    {128, 160, 1, 4.1, 0.64, 0.73, 0.0},
+    {128, 128, 1, 3.6, 0.51, 0.56, 0.0},
+    {64, 128, 2, 2.8, 0.36, 0.62, 0.0},
+    {64, 128, 3, 3.0, 0.48, 0.88, 0.0},  // two stages
+};
+constexpr double kLaunch = 4.0, kGegluLaunch = 2.0;
 constexpr int kMaxSplit = 8;
 constexpr int kMinPieceTiles = 4;  // k-tiles per piece
 
@@ -518,8 +533,9 @@ Choice choose(int M, int outs, int K, bool geglu, int seg, int w_seg_rows, size_
     Choice best{-1, 1, 1e30, 0};
     const int nk = K / KT;
     const int n_xcd = dl.xcd_merge ? dl.n_xcd : 1;
-    for (int i = 0; i < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
-        const Shape& sh = kShapes[i];
+    const int n_shapes = geglu ? sizeof(kGegluShapes) / sizeof(Shape) : sizeof(kShapes) / sizeof(Shape);
+    for (int i = 0; i < n_shapes; ++i) {
+        const Shape& sh = geglu ? kGegluShapes[i] : kShapes[i];
         const int bno = geglu ? sh.bn / 2 : sh.bn;
         if (outs % bno != 0 || (w_seg_rows > 0 && w_seg_rows % sh.bn != 0) || (seg < outs && seg % bno != 0)) continue;
         const int64_t tiles = (int64_t)((M + sh.bm - 1) / sh.bm) * (outs / bno);
@@ -537,7 +553,7 @@ Choice choose(int M, int outs, int K, bool geglu, int seg, int w_seg_rows, size_
             }
             const double rounds = (double)((wgs + slots - 1) / slots);
             const double ktile = wgs > dl.cus ? sh.ktile_shared : sh.ktile;
-            const double us = kLaunch + rounds * (sh.ends + ktile * ((nk + k - 1) / k)) + (k > 1 ? sh.merge : 0.0);
+            const double us = (geglu ? kGegluLaunch : kLaunch) + rounds * (sh.ends + ktile * ((nk + k - 1) / k)) + (k > 1 ? sh.merge : 0.0);
             if (us < best.us) best = Choice{i, k, us, bytes};
         }
     }
@@ -560,9 +576,11 @@ int64_t x_span(const GemmParams& p) {
 
 }  // namespace
 
-void wide_tile(int shape, bool geglu, int32_t& tokens, int32_t& outputs) {
-    tokens = kShapes[shape].bm;
-    outputs = geglu ? kShapes[shape].bn / 2 : kShapes[shape].bn;
+void wide_tile(int shape, bool geglu, int32_t& tokens, int32_t& outputs, int32_t& per_cu) {
+    const Shape& sh = geglu ? kGegluShapes[shape] : kShapes[shape];
+    tokens = sh.bm;
+    outputs = geglu ? sh.bn / 2 : sh.bn;
+    per_cu = sh.share;
 }
 
 size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl) {
@@ -583,7 +601,7 @@ bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& limit_us, int& sha
     const bool ws_ok = p.split_ws != nullptr && ((uintptr_t)p.split_ws & 15u) == 0;
     const Choice c = choose(p.M, p.N, p.K, p.geglu != 0, p.seg, p.w_seg_rows, ws_ok ? p.split_ws_bytes : 0, dl);
     if (c.shape < 0 || c.us >= limit_us) return false;
-    const Shape& sh = kShapes[c.shape];
+    const Shape& sh = p.geglu ? kGegluShapes[c.shape] : kShapes[c.shape];
     const int mt = (p.M + sh.bm - 1) / sh.bm, nt = p.N / (p.geglu ? sh.bn / 2 : sh.bn);
     p.n_tiles = mt * nt;
     p.splitk = c.splitk;
@@ -612,7 +630,12 @@ hipError_t launch_gemm_wide(const GemmParams& p, int shape, hipStream_t s) {
         case 0: return launch_shape<256, 160, 4, 3>(p, s);
         case 1: return launch_shape<128, 160, 4, 4>(p, s);
         case 2: return launch_shape<128, 128, 4, 4>(p, s);
-        default: return launch_shape<64, 128, 2, 3>(p, s);
+        case 3: return launch_shape<64, 128, 2, 3>(p, s);
+        default: {  // GEGLU's own
+            const dim3 grid((unsigned)((int64_t)p.n_xcd * p.tpx));
+            gemm_wide_kernel<64, 128, 2, 2, false, true><<<grid, 64 * 2 * WN, 0, s>>>(p);
+            return hipGetLastError();
+        }
     }
 }
 

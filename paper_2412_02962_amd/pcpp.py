@@ -136,6 +136,7 @@ def _load():
         "pcpp_partial_attention_noalloc": (ctypes.c_int, [gp, vp, vp, vp, vp, vp, vp, vp, vp, vp]),
         "pcpp_partial_attention": (ctypes.c_int, [gp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]),
         "pcpp_transformer_block_workspace_size": (sz, [gp, wp, i32, i32]),
+        "pcpp_geglu_plan": (ctypes.c_int, [gp, i32, i32, i32, vp, i32p, i32p, i32p]),
         "pcpp_transformer_block": (ctypes.c_int, [gp, wp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp, vp,
                                                   vp, sz, vp]),
         "pcpp_transformer_block_sync_gn": (ctypes.c_int, [gp, wp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp,
@@ -178,7 +179,7 @@ EXPORTED = (
     "pcpp_version", "pcpp_strerror", "pcpp_context_rows", "pcpp_gather_context",
     "pcpp_partial_attention_workspace_size", "pcpp_partial_attention", "pcpp_partial_attention_plan",
     "pcpp_partial_attention_noalloc",
-    "pcpp_transformer_block_workspace_size", "pcpp_transformer_block",
+    "pcpp_transformer_block_workspace_size", "pcpp_geglu_plan", "pcpp_transformer_block",
     "pcpp_boundary_bytes", "pcpp_pack_boundary", "pcpp_unpack_boundary", "pcpp_transformer_block_sync_gn",
     "pcpp_partial_attention_multihop_workspace_size", "pcpp_partial_attention_multihop",
     "pcpp_multihop_message_bytes", "pcpp_pack_multihop", "pcpp_unpack_multihop",
@@ -288,6 +289,17 @@ def make_block_weights(tensors: dict, ff_inner: int, gn_groups: int) -> pcpp_blo
 
 def pcpp_transformer_block_workspace_size(g, w, n_text, text_dim) -> int:
     return _lib.pcpp_transformer_block_workspace_size(ctypes.byref(g), ctypes.byref(w), n_text, text_dim)
+
+
+def pcpp_geglu_plan(g, ff_inner, cus=0, cus_enabled=0, stream=None):
+    """(tokens, outputs) of the tiles of a block's GEGLU product and how many of
+    its workgroups share a compute unit; cus, cus_enabled and stream as for
+    pcpp_conv3x3_plan."""
+    bm, bn, k = (ctypes.c_int32() for _ in range(3))
+    st = _stream(stream) if cus == 0 else None
+    _check("pcpp_geglu_plan", _lib.pcpp_geglu_plan(ctypes.byref(g), ff_inner, cus, cus_enabled, st,
+                                                   ctypes.byref(bm), ctypes.byref(bn), ctypes.byref(k)))
+    return bm.value, bn.value, k.value
 
 
 def pcpp_transformer_block(g, w, x, text, n_text, text_dim, k_up, v_up, k_dn, v_dn, y, k_fresh_out,

@@ -61,7 +61,8 @@ def test_split_pieces_give_the_same_bits_again():
 
 # (H, W, n, i, heads, ff_inner, batch): ragged bands and feed-forward widths
 # that take every tile (outputs per GEGLU tile: 80 or 64)
-BLOCKS = [(18, 28, 2, 1, 4, 640, 1), (10, 13, 1, 0, 5, 320, 3), (50, 50, 1, 0, 2, 448, 2), (40, 64, 2, 0, 10, 2560, 2), (64, 64, 2, 1, 10, 2560, 2)]
+BLOCKS = [(18, 28, 2, 1, 4, 640, 1), (10, 13, 1, 0, 5, 320, 3), (50, 50, 1, 0, 2, 448, 2), (40, 64, 2, 0, 10, 2560, 2), (64, 64, 2, 1, 10, 2560, 2),
+          (35, 49, 1, 0, 1, 1280, 1)]
 
 
 @pytest.mark.parametrize("shape", BLOCKS, ids=lambda c: "x".join(map(str, c)))
@@ -81,3 +82,10 @@ def test_block_on_wide_tiles(shape):
     gu.check_composition(gu.to_f64(y), want_y, 6, "y")
     gu.check_composition(gu.to_f64(k), want_k, 4, "k export")
     gu.check_composition(gu.to_f64(v), want_v, 4, "v export")
+
+
+def test_geglu_on_three_tiles_a_compute_unit():
+    """The last of the blocks above: 540 tiles of 64 x 64, the last row of them with 51 tokens."""
+    from paper_2412_02962_amd import pcpp
+    H, W, n, i, heads, ff, batch = BLOCKS[-1]
+    assert pcpp.pcpp_geglu_plan(pcpp.make_geom(H, W, n, i, 0.5, heads, 64, batch), ff) == (64, 64, 3)

@@ -62,3 +62,21 @@ def test_k_is_split_only_on_whole_unmasked_xcds():
         _plan(*geo, cus=-1)
     with pytest.raises(pcpp.PcppError):
         _plan(48, 240, 8, 2, 1920, 65)
+
+
+def _geglu(tokens, heads, ff=None, cus=256, enabled=256):
+    return pcpp.pcpp_geglu_plan(pcpp.make_geom(1, tokens, 1, 0, 0.0, heads), ff or 256 * heads, cus, enabled)
+
+
+def test_geglu_tiles():
+    """Three 64 x 64 tiles to a compute unit where K is short and the tiles
+    come to several rounds; the largest ones for long K and many tokens."""
+    for tokens, heads in ((2072, 5), (8219, 4), (23864, 8), (1157, 8), (11610, 1), (546, 16)):
+        assert _geglu(tokens, heads) == (64, 64, 3), (tokens, heads)
+    assert _geglu(65, 1) == (64, 64, 2)
+    assert _geglu(2048, 10) == _geglu(1024, 20) == _geglu(12639, 20) == (256, 80, 1)
+    assert _geglu(512, 20) == _geglu(504, 20) == (128, 80, 1)
+    assert _geglu(500, 8, 2560) == (128, 64, 1)
+    assert _geglu(2048, 10, 2496)[1] == 64  # 2496 = 39 x 64
+    with pytest.raises(pcpp.PcppError):
+        _geglu(64, 5, 100)
