@@ -774,7 +774,7 @@ __device__ __forceinline__ f32x4 mfma16x16x32(bf16x8 a, bf16x8 b, f32x4 c) {
 }
 
 template <int NS>
-__global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
+__global__ __launch_bounds__(512, NS == 2 ? 6 : 2) void gemm80_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(16))) char lds[NS * G80_STAGE];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -827,10 +827,13 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
     for (int fb = 0; fb < 5; ++fb) acc[fb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Wavefront (tb, 0) finishes blocks 0-2, (tb, 1) blocks 3-4: token
-    // m0 + 16 tb + lane % 16, W rows n0 + 16 fb + 4 (lane / 16) + 0..3.  Their
-    // bias and residual are loaded here, behind the products: after them the
-    // loads' trip to memory adds to every launch (1024 x 1280 x 1280 with a
-    // float32 residual 11.96 -> 11.56 us, 4096 x 640 x 640 13.8 -> 13.1).
+    // m0 + 16 tb + lane % 16, W rows n0 + 16 fb + 4 (lane / 16) + 0..3.  With one
+    // tile per compute unit their bias and residual are loaded here, behind the
+    // products: after them the loads' trip to memory adds to every launch
+    // (1024 x 1280 x 1280 with a float32 residual 11.96 -> 11.56 us, 4096 x 640 x
+    // 640 13.8 -> 13.1).  Held through the loop they take 17 registers, and with
+    // two stages a third workgroup would no longer fit its compute unit (80
+    // registers): 4096 x 960 x 320 8.9 -> 11.6 us; there they are loaded after it.
     auto owned = [&](int fb) { return kg == 0 ? fb < 3 : fb >= 3; };
     const int m = m0 + 16 * tb + (lane & 15);
     const int mc = min(m, p.M - 1);
@@ -838,20 +841,24 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
     f32x4 res_v[3] = {};
     const int nl = n0 + 4 * (lane >> 4);
     auto row_of = [&](int i) { return nl + 16 * min(3 * kg + i, 4); };  // (tb, 1): its second block twice
-    if (p.bias != nullptr) {
+    auto load_addends = [&]() {
+        if (p.bias != nullptr) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) bias_v[i] = *(const bf16x4*)(p.bias + row_of(i));
-    }
-    if (p.resid != nullptr && p.resid_f32) {
-        const float* r = (const float*)p.resid + (int64_t)mc * p.ldr;
+            for (int i = 0; i < 3; ++i) bias_v[i] = *(const bf16x4*)(p.bias + row_of(i));
+        }
+        if (p.resid != nullptr && p.resid_f32) {
+            const float* r = (const float*)p.resid + (int64_t)mc * p.ldr;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) res_v[i] = *(const f32x4*)(r + row_of(i));
-    }
-    if (p.resid != nullptr && !p.resid_f32) {
-        const bf16* r = (const bf16*)p.resid + (int64_t)mc * p.ldr;
+            for (int i = 0; i < 3; ++i) res_v[i] = *(const f32x4*)(r + row_of(i));
+        }
+        if (p.resid != nullptr && !p.resid_f32) {
+            const bf16* r = (const bf16*)p.resid + (int64_t)mc * p.ldr;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) res_h[i] = *(const bf16x4*)(r + row_of(i));
-    }
+            for (int i = 0; i < 3; ++i) res_h[i] = *(const bf16x4*)(r + row_of(i));
+        }
+    };
+    constexpr bool EARLY = NS > 2;
+    if constexpr (EARLY) load_addends();
 
 #pragma unroll
     for (int st = 0; st < NS - 1; ++st)
@@ -882,6 +889,8 @@ __global__ __launch_bounds__(512) void gemm80_kernel(GemmParams p) {
         asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w4));
         acc[4] = mfma16x16x32(__builtin_bit_cast(bf16x8, w4), __builtin_bit_cast(bf16x8, x), acc[4]);
     }
+
+    if constexpr (!EARLY) load_addends();
 
     // The two k-steps' sums: each wavefront hands its partner the sums of the
     // partner's blocks.
