@@ -145,6 +145,17 @@ GemmParams gemm(const void* a, int64_t lda, bool a_f32, const void* wt, const vo
     return p;
 }
 
+// Whether proj_in applies the GroupNorm itself, from the statistics launch's
+// records: one launch less, but each of its workgroups merges the records and
+// makes the tables, so only up to 640 channels and two 64 x 64 tiles a compute
+// unit.  Statistics to proj_in, with the text K/V beside it: 256 x 128 18.7 us
+// with an apply launch, 14.1 staged; 4096 x 320 24.8 and 18.7; 2048 x 512 25.5
+// and 20.5; 2048 x 640 26.0 and 22.4; past the line 4096 x 640 33.3 and 34.3,
+// 14336 x 512 46.5 and 57.4, 2048 x 1024 50.5 and 54.2.
+bool gn_staged(int rows, int N, int C, int cus) {
+    return N % 64 == 0 && C % 64 == 0 && C <= GEMM_GN_MAXC && (int64_t)(rows / 64) * (C / 64) <= 2 * (int64_t)cus;
+}
+
 // u [M, F] = value * GELU(gate), W rows 0 .. F - 1 the values, F .. 2 F - 1 the gates.
 GemmParams geglu(const void* a, const void* wt, const void* bias, int M, int F, int K, void* u) {
     GemmParams p = gemm(a, K, false, wt, bias, M, F, K, u, F, false);
@@ -297,8 +308,8 @@ int run_module(const pcpp_geom_t* g, const ModuleW& mw, const pcpp_basic_block_w
     // The attention launches' work counters too: the workspace may hold
     // anything on entry (a caller may share it with calls that use it as
     // plain scratch), and every launch below leaves its counters at zero.
+    const DeviceLayout dl = device_layout(s);
     {
-        const DeviceLayout dl = device_layout(s);
         const AttnParams sa = self_attn_params(g, r, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                                nullptr, nullptr);
         const AttnParams ca = cross_attn_params(g, r, nullptr, nullptr, nullptr, nullptr, n_text);
@@ -308,9 +319,26 @@ int run_module(const pcpp_geom_t* g, const ModuleW& mw, const pcpp_basic_block_w
     }
     // proj_in, and beside it (in the same launch where that is faster) the
     // first chunk's text K/V, independent of the band.
-    PCPP_CHECK(launch_group_norm(gp, s));
     {
-        const GemmParams pin = gemm(t16, C, false, mw.proj_in_w, mw.proj_in_b, rows, C, C, hid, C, true);
+        GemmParams pin = gemm(t16, C, false, mw.proj_in_w, mw.proj_in_b, rows, C, C, hid, C, true);
+        if (gn_staged(rows, N, C, dl.cus)) {
+            PCPP_CHECK(launch_group_norm_stats(gp, s));
+            pin.a = x;
+            pin.gn.stats = gp.stats;
+            pin.gn.chunks = gp.chunks;
+            pin.gn.G = gp.G;
+            pin.gn.B = gp.B;
+            pin.gn.eps = gp.eps;
+            pin.gn.bands = gp.bands;
+            pin.gn.n_bands = gp.n_bands;
+            pin.gn.band = gp.band;
+            pin.gn.own_out = gp.own_out;
+            pin.gn_gamma = gp.gamma;
+            pin.gn_beta = gp.beta;
+            pin.gn_N = N;
+        } else {
+            PCPP_CHECK(launch_group_norm(gp, s));
+        }
         PCPP_CHECK(L.kv_grouped && depth > 0 ? gemm_pair_s(pin, text_kv(0)) : gemm_s(pin));
     }
 

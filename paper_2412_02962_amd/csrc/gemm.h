@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gn_merge.h"
 #include "kernels.h"
 
 namespace pcpp {
@@ -68,7 +69,21 @@ struct GemmParams {
     // Set by launch_gemm for a split launch.
     int32_t splitk = 1, n_xcd = 1, tpx = 0, n_tiles = 0;
     int32_t m_group = 1;  // wide tiles: token tiles whose W tiles are walked together
+    // (Last: what the kernels read of their arguments lies close together.)
+    // gn_N > 0: GroupNorm of X applied while X is staged (bf16 X; K = C <=
+    // GEMM_GN_MAXC channels, G <= 256 groups; gn_N tokens per image, a
+    // multiple of 64): channel k of token m becomes X * sc + sh with the
+    // scale and shift of m's image, from the statistics launch's records in
+    // gn (and the other bands' for the synchronized form), in the arithmetic
+    // of the GroupNorm apply kernel (the same bits).  Runs on the 64 x 64
+    // pipelined kernel, unsplit; the workgroup with image b's first token tile
+    // and the first W tile writes the band's own statistics to gn.own_out.
+    GnStatsSrc gn = {};
+    const __bf16* gn_gamma = nullptr;
+    const __bf16* gn_beta = nullptr;
+    int32_t gn_N = 0;
 };
+constexpr int GEMM_GN_MAXC = 640;
 constexpr int GEMM_XA_MAXT = 96;  // keys of the cross-attention epilogue
 
 // Bytes of split-K workspace a GEMM of this shape can use (0: it runs
@@ -143,6 +158,9 @@ size_t group_norm_ws_bytes(int B, int G, int N);
 bool norm_shapes_ok(int C, int G);  // GroupNorm and LayerNorm: C <= 2048
 bool gn_shapes_ok(int C, int G);    // GroupNorm alone: C <= 2560
 hipError_t launch_group_norm(GroupNormParams p, hipStream_t s);
+// The statistics launch alone (sets p.chunks); a product that applies
+// GroupNorm while staging its operand follows (GemmParams::gn_N).
+hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s);
 
 // LayerNorm over the channel axis of fp32 rows, bf16 output.
 struct LayerNormParams {

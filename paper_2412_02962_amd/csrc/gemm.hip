@@ -277,16 +277,24 @@ __device__ __forceinline__ void wait_tiles_after(int later) {
     }
 }
 
-// LDS floats of the cross-attention epilogue's K rows and transposed V.
+// LDS floats of the cross-attention epilogue's K rows and transposed V, and
+// of GroupNorm staging's scale and shift per channel and statistics per group.
 constexpr int XA_TAB_FLOATS = (GEMM_XA_MAXT * 128 + 64 * 200) / 4;
+constexpr int GN_TAB_FLOATS = 2 * GEMM_GN_MAXC + 2 * 256;
+
+// What a pipelined launch does besides the product: nothing, an implicit
+// convolution, the cross-attention epilogue, GroupNorm staging.
+enum DmaForm { DMA_PLAIN, DMA_CONV, DMA_XATT, DMA_GN };
+constexpr int tab_floats(int form) { return form == DMA_XATT ? XA_TAB_FLOATS : form == DMA_GN ? GN_TAB_FLOATS : 4; }
 
 // One workgroup's tile of the product; (bx, by) is its place in the
-// product's own grid (blockIdx of a single launch); lds holds NS stages,
-// xa_tab XA_TAB_FLOATS floats with XATT (the cross-attention epilogue).
-template <int BM, int BN, int NS, bool CONV, bool XATT>
+// product's own grid (blockIdx of a single launch); lds holds NS stages, tab
+// tab_floats(FORM) floats.
+template <int BM, int BN, int NS, int FORM>
 __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx, const int by, char* lds,
-                                              float* xa_tab) {
-    static_assert(!XATT || (BM == 64 && BN == 64 && !CONV), "plain 64 x 64 tiles only");
+                                              float* tab) {
+    constexpr bool CONV = FORM == DMA_CONV, XATT = FORM == DMA_XATT, AGN = FORM == DMA_GN;
+    static_assert(!(XATT || AGN) || (BM == 64 && BN == 64), "64 x 64 tiles only");
     constexpr int WMB = BM / 64;                      // 32-token blocks per wavefront
     constexpr int WNB = BN / 64;                      // 32-row W blocks per wavefront
     constexpr int XP = BM / 32;                       // 1 KB X pieces per wavefront per k-tile
@@ -464,12 +472,12 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
     };
 
-    // Cross-attention.  xa_tab holds K_h as rows of 128 bytes (the
+    // Cross-attention.  tab holds K_h as rows of 128 bytes (the
     // operand swizzle; keys past xa_T zero) and V_h transposed, a row of
     // 200 bytes per head dimension (keys along the row; 200 keeps the eight-
     // byte reads of 32 dimensions on distinct banks).
     constexpr int XA_VT_STRIDE = 200;
-    char* xa = (char*)xa_tab;
+    char* xa = (char*)tab;
     char* xa_vt = xa + GEMM_XA_MAXT * 128;
     auto xatt_stage = [&]() {
         const int img = m0 / p.xa_N;
@@ -616,16 +624,72 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         if (p.splitk == 1) load_addends();
     }
 
+    // GroupNorm staging.  X arrives with the direct loads like W; after the
+    // products of k-tile kt each lane rewrites in place the 16-byte pieces of
+    // k-tile kt + 1 that its own loads brought (so that its own wait suffices),
+    // published by the next barrier.  Piece i of the lane: row 8 (wave + 4 i)
+    // + lane / 8, source chunk (lane % 8) ^ ((row / 2) % 8).
+    float* const sc = tab;
+    float* const sh = tab + GEMM_GN_MAXC;
+    auto gn_rewrite = [&](int kt, int stage) {
+#pragma unroll
+        for (int i = 0; i < XP; ++i) {
+            const int r = 8 * (wave + 4 * i) + (lane >> 3);
+            const int c0 = kt * DBK + 8 * ((lane & 7) ^ ((r >> 1) & 7));
+            bf16x8* at = (bf16x8*)(lds + stage * STAGE + (wave + 4 * i) * 1024 + lane * 16);
+            const bf16x8 v = *at;
+            bf16x8 y;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 a = *(const f32x4*)(sc + c0 + 4 * h), b = *(const f32x4*)(sh + c0 + 4 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[4 * h + e] = f32_to_bf16(__builtin_fmaf((float)v[4 * h + e], a[e], b[e]));
+            }
+            *at = y;
+        }
+    };
+    // X of the k-tile before the newest: behind it its own W and, if issued, a k-tile.
+    auto wait_x = [&](bool one_more) {
+        if (one_more)
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP + PT));
+        else
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP));
+    };
+
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
         if (kt0 + s < kt1) issue(kt0 + s, s);
     if constexpr (XATT) xatt_stage();  // its loads wait behind the first k-tiles'
+    if constexpr (AGN) {               // the statistics are merged while the first k-tiles are in flight
+        static_assert(NS == 3, "wait_x");
+        const int img = m0 / p.gn_N;
+        float* g_mean = tab + 2 * GEMM_GN_MAXC;
+        float* g_rstd = g_mean + 256;
+        gn_group_stats(p.gn, img, m0 == img * p.gn_N && n0 == 0, g_mean, g_rstd);
+        const int cg = p.K / p.gn.G;
+        for (int c = tid; c < p.K; c += 256) {
+            const int g = c / cg;
+            const float a = g_rstd[g] * bf16_to_f32(p.gn_gamma[c]);
+            sc[c] = a;
+            sh[c] = bf16_to_f32(p.gn_beta[c]) - g_mean[g] * a;
+        }
+        __syncthreads();
+        wait_x(kt0 + 1 < kt1);
+        gn_rewrite(kt0, 0);
+    }
     for (int kt = kt0; kt < kt1; ++kt) {
         // k-tiles issued after kt so far: min(kt1 - 1 - kt, NS - 2), PT loads each
         wait_tiles_after<PT, NS - 2>(min(kt1 - 1 - kt, NS - 2));
+        if constexpr (AGN) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this lane's rewrite of X(kt)
         __builtin_amdgcn_s_barrier();  // everyone's pieces of tile kt landed; the stage of tile kt-1 is free
         if (kt + NS - 1 < kt1) issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
         mfma_tile(lds0 + ((kt - kt0) % NS) * STAGE);
+        if constexpr (AGN) {
+            if (kt + 1 < kt1) {
+                wait_x(kt + 2 < kt1);
+                gn_rewrite(kt + 1, (kt - kt0 + 1) % NS);
+            }
+        }
     }
 
     if constexpr (XATT) {
@@ -725,15 +789,15 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     }
 }
 
-template <int BM, int BN, int NS, bool CONV, bool XATT>
+template <int BM, int BN, int NS, int FORM>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
-    __shared__ __attribute__((aligned(16))) float xa_tab[XATT ? XA_TAB_FLOATS : 4];
-    gemm_dma_body<BM, BN, NS, CONV, XATT>(p, blockIdx.x, blockIdx.y, lds, xa_tab);
+    __shared__ __attribute__((aligned(16))) float tab[tab_floats(FORM)];
+    gemm_dma_body<BM, BN, NS, FORM>(p, blockIdx.x, blockIdx.y, lds, tab);
 }
 
-// Two independent plain products in one launch (so that neither pays a
-// launch's fixed cost alone): workgroups [0, n_a) run `a`, [b0, b0 + n_b)
+// Two independent products, the second plain, in one launch (so that neither
+// pays a launch's fixed cost alone): workgroups [0, n_a) run `a`, [b0, b0 + n_b)
 // run `b`, each product's grid linearised x-fastest; b0 is a multiple of the
 // XCD count, so a product on XCD-ordered tiles keeps its workgroup-to-XCD
 // map; the workgroups in between exit at once.
@@ -742,14 +806,15 @@ struct GemmPair {
     int32_t gx_a, n_a, gx_b, b0;
 };
 
-template <int BM, int BN, int NS>
+template <int BM, int BN, int NS, int FORM_A>
 __global__ __launch_bounds__(256) void gemm_dma_pair_kernel(GemmPair pp) {
     __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
+    __shared__ __attribute__((aligned(16))) float tab[tab_floats(FORM_A)];
     const int id = blockIdx.x;
     if (id < pp.n_a)
-        gemm_dma_body<BM, BN, NS, false, false>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, nullptr);
+        gemm_dma_body<BM, BN, NS, FORM_A>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, tab);
     else if (id >= pp.b0)
-        gemm_dma_body<BM, BN, NS, false, false>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, nullptr);
+        gemm_dma_body<BM, BN, NS, DMA_PLAIN>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -937,11 +1002,13 @@ hipError_t launch_dma64(const GemmParams& p, hipStream_t s) {
     dim3 grid((p.M + 63) / 64, p.N / 64);
     if (p.tpx > 0) grid = dim3((unsigned)(p.n_xcd * p.tpx * p.splitk), 1);
     if (p.xa_T > 0)
-        gemm_dma_kernel<64, 64, 3, false, true><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<64, 64, 3, DMA_XATT><<<grid, 256, 0, s>>>(p);
+    else if (p.gn_N > 0)
+        gemm_dma_kernel<64, 64, 3, DMA_GN><<<grid, 256, 0, s>>>(p);
     else if (p.conv_W > 0)
-        gemm_dma_kernel<64, 64, 3, true, false><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<64, 64, 3, DMA_CONV><<<grid, 256, 0, s>>>(p);
     else
-        gemm_dma_kernel<64, 64, 3, false, false><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<64, 64, 3, DMA_PLAIN><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -1040,6 +1107,13 @@ hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
             p.xa_ldkv % 8 != 0)
             return hipErrorInvalidValue;
     }
+    if (p.gn_N != 0) {  // GroupNorm staging: the 64 x 64 pipelined kernel, unsplit
+        if (p.a_f32 || p.geglu || p.conv_W > 0 || p.xa_T != 0 || p.K % DBK != 0 || p.K > GEMM_GN_MAXC ||
+            p.N % 64 != 0 || p.seg % 4 != 0 || p.gn_N <= 0 || p.gn_N % 64 != 0 || p.M % p.gn_N != 0 || p.gn.G < 1 ||
+            p.gn.G > 256 || p.K % p.gn.G != 0 || p.gn.stats == nullptr || p.gn_gamma == nullptr ||
+            p.gn_beta == nullptr)
+            return hipErrorInvalidValue;
+    }
     if (p.w_seg_rows != 0 || p.seg_stride != 0) {  // the pipelined kernel's plain form only
         if (p.a_f32 || p.geglu || p.conv_W > 0 || p.K % DBK != 0 || p.seg % 4 != 0 || p.N % 64 != 0 ||
             p.seg_stride < 0 || p.w_seg_rows < 0)
@@ -1067,7 +1141,7 @@ hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
     };
     // bf16 X with K % 64 == 0: the pipelined kernels.
     if (!p.a_f32 && p.K % DBK == 0 && p.seg % 4 == 0) {
-        if (!p.geglu && p.conv_W == 0 && p.split_ws != nullptr && p.N % 64 == 0 && p.xa_T == 0) {
+        if (!p.geglu && p.conv_W == 0 && p.split_ws != nullptr && p.N % 64 == 0 && p.xa_T == 0 && p.gn_N == 0) {
             const SplitPlan sp = split_plan_plain(p.M, p.N, p.K, dl);
             if (sp.splitk > 1 && p.split_ws_bytes >= sp.bytes && ((uintptr_t)p.split_ws & 15u) == 0) {
                 p.splitk = sp.splitk;
@@ -1088,7 +1162,7 @@ hipError_t plan_narrow(GemmParams& p, const DeviceLayout& dl, GemmKind& kind) {
             // four times X's rows: those keep the XCD-contiguous 64 x 64 tiles.
             const int64_t mt64 = (p.M + 63) / 64;
             const int64_t t80 = p.N % 80 == 0 ? mt64 * (p.N / 80) : 0;
-            const bool g80_form = p.xa_T == 0 && p.conv_W == 0 && p.w_seg_rows == 0 && p.seg_stride == 0 &&
+            const bool g80_form = p.xa_T == 0 && p.gn_N == 0 && p.conv_W == 0 && p.w_seg_rows == 0 && p.seg_stride == 0 &&
                                   p.bias2 == nullptr && (p.seg >= p.N || (p.seg % 80 == 0 && p.N / p.seg <= 3));
             if (g80_form && p.N < 4 * (int64_t)p.M && t80 > 0 && t80 <= 3 * dl.cus && 4 * t80 >= 3 * (int64_t)dl.cus &&
                 mt64 * (p.N / 64) > dl.cus) {
@@ -1242,7 +1316,7 @@ hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipS
         a64.splitk = 1;
         a64.tpx = 0;
     }
-    if (pb.kind == GK_DMA_64 && b.conv_W == 0 && b.xa_T == 0 && plain_a && !(a64.splitk > 1 && b.splitk > 1)) {
+    if (pb.kind == GK_DMA_64 && b.conv_W == 0 && b.xa_T == 0 && b.gn_N == 0 && plain_a && !(a64.splitk > 1 && b.splitk > 1)) {
         auto work = [](const GemmParams& p) {
             return (double)((p.M + 63) / 64) * (p.N / 64) * (p.K / DBK);
         };
@@ -1250,7 +1324,7 @@ hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipS
         const double longest = fmax((double)(a64.K / DBK) / a64.splitk, (double)(b.K / DBK) / b.splitk);
         const double us = 5.8 + (a64.splitk > 1 || b.splitk > 1 ? 3.0 : 0.0) +
                           0.30 * (wgs > dl.cus ? fmax(longest, (work(a64) + work(b)) / dl.cus) : longest);
-        if (us < pa.us + pb.us) {
+        if (us < pa.us + pb.us || a.gn_N > 0) {
             GemmPair pp;
             pp.a = a64;
             pp.b = b;
@@ -1262,7 +1336,10 @@ hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipS
             pp.b0 = (pp.n_a + n_xcd - 1) / n_xcd * n_xcd;
             const int64_t total = (int64_t)pp.b0 + (int64_t)pp.gx_b * gy_b;
             if (total > INT32_MAX) return hipErrorInvalidValue;
-            gemm_dma_pair_kernel<64, 64, 3><<<dim3((unsigned)total), 256, 0, s>>>(pp);
+            if (a.gn_N > 0)
+                gemm_dma_pair_kernel<64, 64, 3, DMA_GN><<<dim3((unsigned)total), 256, 0, s>>>(pp);
+            else
+                gemm_dma_pair_kernel<64, 64, 3, DMA_PLAIN><<<dim3((unsigned)total), 256, 0, s>>>(pp);
             return hipGetLastError();
         }
     }

@@ -589,7 +589,7 @@ size_t wide_split_bytes(int M, int N, int K, const DeviceLayout& dl) {
 }
 
 bool plan_wide(GemmParams& p, const DeviceLayout& dl, double& limit_us, int& shape) {
-    if (p.a_f32 || p.xa_T != 0 || p.K % KT != 0 || p.M < 1 || p.ldo % 8 != 0 ||
+    if (p.a_f32 || p.xa_T != 0 || p.gn_N != 0 || p.K % KT != 0 || p.M < 1 || p.ldo % 8 != 0 ||
         (p.resid != nullptr && p.ldr % 8 != 0))
         return false;
     if (p.geglu && (p.resid != nullptr || p.out_bf16 != nullptr || p.bias2 != nullptr || p.seg < p.N ||

@@ -507,7 +507,7 @@ bool gn_shapes_ok(int C, int G) {
 
 bool norm_shapes_ok(int C, int G) { return gn_shapes_ok(C, G) && C <= 4 * 64 * LN_MAX_VEC; }
 
-static hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
+hipError_t launch_group_norm_stats(GroupNormParams& p, hipStream_t s) {
     if (!gn_shapes_ok(p.C, p.G)) return hipErrorInvalidValue;
     if (p.pad_W < 0 || (p.pad_W > 0 && p.N % p.pad_W != 0)) return hipErrorInvalidValue;
     const SlabPlan sp = slab_plan(p.B, p.N, p.C, p.G, device_layout(s).cus);
