@@ -31,3 +31,11 @@ int check_attention(const pcpp_geom_t* g, Geo* r, const void* q, const void* k_f
                     const void* k_up, const void* v_up, const void* k_dn, const void* v_dn, const void* out);
 
 }  // namespace pcpp
+
+// pcpp_conv3x3_export with a limit on the looks that the pieces of a split
+// tile take at each other (GemmParams::max_polls; < 0: the library's own).
+// Exported for the tests of the pieces that give up waiting; not part of the C
+// ABI.
+extern "C" __attribute__((visibility("default"))) int pcpp_internal_conv3x3(
+    const pcpp_conv_geom_t* g, const void* x, const void* row_up, const void* row_dn, const void* w, const void* bias,
+    void* y, void* first_out, void* last_out, void* workspace, size_t ws_bytes, int32_t max_polls, void* stream);

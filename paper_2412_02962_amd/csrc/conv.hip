@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "../../include/pcpp.h"
+#include "api_internal.h"
 #include "common.h"
 #include "gemm.h"
 #include "kernels.h"
@@ -174,9 +175,10 @@ PCPP_EXPORT int pcpp_conv3x3_plan(const pcpp_conv_geom_t* g, int32_t cus, int32_
     return PCPP_OK;
 }
 
-PCPP_EXPORT int pcpp_conv3x3_export(const pcpp_conv_geom_t* g, const void* x, const void* row_up,
-                                    const void* row_dn, const void* w, const void* bias, void* y, void* first_out,
-                                    void* last_out, void* workspace, size_t ws_bytes, void* stream) {
+PCPP_EXPORT int pcpp_internal_conv3x3(const pcpp_conv_geom_t* g, const void* x, const void* row_up,
+                                      const void* row_dn, const void* w, const void* bias, void* y, void* first_out,
+                                      void* last_out, void* workspace, size_t ws_bytes, int32_t max_polls,
+                                      void* stream) {
     int st = validate_conv(g);
     if (st != PCPP_OK) return st;
     const bool need_up = g->patch_idx > 0;
@@ -220,7 +222,14 @@ PCPP_EXPORT int pcpp_conv3x3_export(const pcpp_conv_geom_t* g, const void* x, co
     GemmParams p = conv_params(g, L, framed, w, bias, y);
     p.split_ws = split_ws;
     p.split_ws_bytes = L.split_bytes;
+    if (max_polls >= 0) p.max_polls = max_polls;
     return launch_gemm(p, s) == hipSuccess ? PCPP_OK : PCPP_EHIP;
+}
+
+PCPP_EXPORT int pcpp_conv3x3_export(const pcpp_conv_geom_t* g, const void* x, const void* row_up,
+                                    const void* row_dn, const void* w, const void* bias, void* y, void* first_out,
+                                    void* last_out, void* workspace, size_t ws_bytes, void* stream) {
+    return pcpp_internal_conv3x3(g, x, row_up, row_dn, w, bias, y, first_out, last_out, workspace, ws_bytes, -1, stream);
 }
 
 PCPP_EXPORT int pcpp_conv3x3(const pcpp_conv_geom_t* g, const void* x, const void* row_up, const void* row_dn,

@@ -69,6 +69,9 @@ struct GemmParams {
     // Set by launch_gemm for a split launch.
     int32_t splitk = 1, n_xcd = 1, tpx = 0, n_tiles = 0;
     int32_t m_group = 1;  // wide tiles: token tiles whose W tiles are walked together
+    // Looks that a piece of a split wide tile takes at the others' arrivals
+    // before it leaves its share to the last of them: about a millisecond.
+    int32_t max_polls = 4096;
     // (Last: what the kernels read of their arguments lies close together.)
     // gn_N > 0: GroupNorm of X applied while X is staged (bf16 X; K = C <=
     // GEMM_GN_MAXC channels, G <= 256 groups; gn_N tokens per image, a

@@ -40,7 +40,6 @@ namespace {
 
 constexpr int KT = 64;        // K per tile
 constexpr int WN = 2;         // wavefronts along the W rows
-constexpr int MAX_POLLS = 4096;  // about a millisecond
 
 typedef __attribute__((address_space(3))) void* lptr;
 
@@ -414,7 +413,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_wide_kernel(GemmParams p) {
             int zero = 0;
             asm volatile("" : "+v"(zero));
             bool all = false;
-            for (int it = 0; !all && it < MAX_POLLS; ++it) {
+            for (int it = 0; !all && it < p.max_polls; ++it) {
                 __builtin_amdgcn_s_sleep(1);
                 all = (l2_add(cnt, zero) & 255) == k;
             }
