@@ -548,7 +548,9 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // us: the launch's time, for the choice between the two forms.  One wave: 6
 // and the cost above.  Several: 2 + waves x (1.05 x tiles + 7), within 5 % of
 // 45 us (2048 x 2662 x 20 heads), 127 (4096 x 10649 x 10), 257 (8192 x 10649
-// x 10) and 2830 (28800 x 37440 x 10), 8 % below 453 (7200 x 9360 x 20).
+// x 10) and 2830 (28800 x 37440 x 10), 8 % below 453 (7200 x 9360 x 20).  (The
+// card of these fits and of pick_k_wide's ran up to 2 % slower than that of
+// make_plan's figures.)
 constexpr int64_t TILE_COST_SHARED = 100;
 constexpr int64_t TILE_COST_ALONE = 64;
 constexpr int64_t PIECE_COST = 257;
@@ -651,8 +653,8 @@ Plan make_form(const AttnParams& p, const DeviceLayout& d, int qb, int64_t max_p
 }
 
 // Blocks of 256 queries where the estimate is 4 % below that of blocks of 128
-// (the estimates' own error): 443 -> 379 us at 7200 x 9360 x 20 heads, 2797
-// -> 2665 at 28800 x 37440 x 10, 254 -> 246 at 8192 x 10649 x 10; not at 2048
+// (the estimates' own error): 453 -> 374 us at 7200 x 9360 x 20 heads, 2780
+// -> 2664 at 28800 x 37440 x 10, 252 -> 243 at 8192 x 10624 x 10; not at 2048
 // x 3072 x 10, batch 2 (47.4 and 47.6), and not where the blocks do not fill
 // the compute units twice (2048 x 2662 x 10: 23.7 and 29.1).
 // Its partial results get the other form's workspace.  Only where that is

@@ -18,8 +18,8 @@
 // run, which the other wavefront of the SIMD fills with its softmax.  K and V
 // operands are read once for both blocks (half the LDS reads and half the
 // staging per query), into the registers whose last use has just been
-// issued.  About 400 cycles: 28800 x 37440 x 10 heads 2797 -> 2666 us, 7200 x
-// 9360 x 20 heads 443 -> 390 us.  (One workgroup per compute unit: 3660 us;
+// issued.  About 400 cycles: 28800 x 37440 x 10 heads 2780 -> 2664 us, 7200 x
+// 9360 x 20 heads 453 -> 374 us (replayed in turn on one card).  (One workgroup per compute unit: 3660 us;
 // products and softmax interleaved one by one: 2816; products at high
 // priority or not, in runs of two, four or eight: within 1 %.)
 //

@@ -8,8 +8,9 @@
 // frame_copy writes the band (upsampled for UP) into a [B][Hf+2][Wf+2][C]
 // buffer with the neighbour rows on top and bottom (upsampled for UP; zeros
 // at the image's edges) and zero side columns; the implicit-GEMM convolution
-// of gemm_dma_kernel then reads every tap at one constant offset from a
-// token's framed position (stride 2: from (2y, 2x)).
+// (gemm_wide_kernel, or gemm_dma_kernel where its 64 x 64 tiles are estimated
+// to be faster) then reads every tap at one constant offset from a token's
+// framed position (stride 2: from (2y, 2x)).
 
 #include <stdint.h>
 

@@ -243,11 +243,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmParams p) {
 // in flight), MFMA operands are read with explicit LDS waits one k-step
 // ahead.  LDS rows are 128 bytes with the 16-byte chunk c of row r stored at
 // slot c ^ ((r >> 1) & 7), so 32 consecutive rows read at one chunk are
-// conflict-free.  Workgroup: 4 wavefronts in a 2 x 2 layout, each
-// computing (BM/2) tokens x (BN/2) W rows.
+// conflict-free.  64 x 64 tiles, 4 wavefronts in a 2 x 2 layout, each
+// computing 32 tokens x 32 W rows.
 // ---------------------------------------------------------------------------
 
 constexpr int DBK = 64;
+constexpr int DT = 64;                     // tokens and W rows of a tile
+constexpr int DNS = 3;                     // stages
+constexpr int DSTAGE = 2 * DT * DBK * 2;  // bytes per stage
 
 typedef const __attribute__((address_space(1))) void* gvoid;
 typedef __attribute__((address_space(3))) void* lvoid;
@@ -288,21 +291,15 @@ enum DmaForm { DMA_PLAIN, DMA_CONV, DMA_XATT, DMA_GN };
 constexpr int tab_floats(int form) { return form == DMA_XATT ? XA_TAB_FLOATS : form == DMA_GN ? GN_TAB_FLOATS : 4; }
 
 // One workgroup's tile of the product; (bx, by) is its place in the
-// product's own grid (blockIdx of a single launch); lds holds NS stages, tab
-// tab_floats(FORM) floats.
-template <int BM, int BN, int NS, int FORM>
+// product's own grid (blockIdx of a single launch); lds holds DNS stages,
+// tab tab_floats(FORM) floats.
+template <int FORM>
 __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx, const int by, char* lds,
                                               float* tab) {
     constexpr bool CONV = FORM == DMA_CONV, XATT = FORM == DMA_XATT, AGN = FORM == DMA_GN;
-    static_assert(!(XATT || AGN) || (BM == 64 && BN == 64), "64 x 64 tiles only");
-    constexpr int WMB = BM / 64;                      // 32-token blocks per wavefront
-    constexpr int WNB = BN / 64;                      // 32-row W blocks per wavefront
-    constexpr int XP = BM / 32;                       // 1 KB X pieces per wavefront per k-tile
-    constexpr int WP = BN / 32;
-    constexpr int PT = XP + WP;                       // loads per thread per k-tile
-    constexpr int STAGE = (BM + BN) * DBK * 2;        // bytes per stage
-    constexpr int NOPS = WNB + WMB;                   // operand reads per k-step
-    static_assert((NS - 2) * PT <= 63, "vmcnt holds at most 63 loads");
+    constexpr int XP = DT / 32;   // 1 KB pieces of X per wavefront per k-tile, and of W
+    constexpr int PT = 2 * XP;    // loads per thread per k-tile
+    static_assert(DNS == 3 && (DNS - 2) * PT <= 63, "wait_x; vmcnt holds at most 63 loads");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -324,12 +321,12 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         piece = j - tl * p.splitk;
         tile = xcd * p.tpx + tl;
         if (tl >= p.tpx || tile >= p.n_tiles) return;  // idle slot of the last XCD (uniform)
-        const int mt = (p.M + BM - 1) / BM;
+        const int mt = (p.M + DT - 1) / DT;
         n_tile = tile / mt;
         m_tile = tile - n_tile * mt;
     }
-    const int m0 = m_tile * BM;
-    const int n0 = n_tile * BN;
+    const int m0 = m_tile * DT;
+    const int n0 = n_tile * DT;
     const int nk_all = p.K / DBK;
     const int kt0 = (int)((int64_t)nk_all * piece / p.splitk);
     const int kt1 = (int)((int64_t)nk_all * (piece + 1) / p.splitk);
@@ -337,7 +334,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     // Per-lane global source of each staged piece (row 8q + (lane >> 3),
     // chunk (lane & 7) ^ swizzle), k offset added per k-tile.
     const char* xsrc[XP];
-    const char* wsrc[WP];
+    const char* wsrc[XP];
     const int cin = CONV ? p.K / 9 : 0;
 #pragma unroll
     for (int i = 0; i < XP; ++i) {
@@ -368,7 +365,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         iss_xoff = ((int64_t)(ky * (p.conv_W + 2) + iss_kx) * cin + iss_cb * DBK) * 2;
     }
     // W of this tile: one of several matrices when w_seg_rows > 0 (a tile's
-    // BN rows never straddle two of them).
+    // rows never straddle two of them).
     const __bf16* wmat = p.w;
     int wrow0 = n0;
     if (p.w_seg_rows > 0) {
@@ -377,13 +374,13 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         wrow0 = n0 - j * p.w_seg_rows;
     }
 #pragma unroll
-    for (int i = 0; i < WP; ++i) {
+    for (int i = 0; i < XP; ++i) {
         const int r = 8 * (wave + 4 * i) + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
         wsrc[i] = (const char*)wmat + ((int64_t)(wrow0 + r) * p.K + 8 * c) * 2;
     }
     auto issue = [&](int kt, int stage) {
-        char* st = lds + stage * STAGE;
+        char* st = lds + stage * DSTAGE;
         const int koff = kt * DBK * 2;
         const int64_t xoff = CONV ? iss_xoff : koff;
         if constexpr (CONV) {
@@ -403,8 +400,8 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         for (int i = 0; i < XP; ++i)
             __builtin_amdgcn_global_load_lds((gvoid)(xsrc[i] + xoff), (lvoid)(st + (wave + 4 * i) * 1024), 16, 0, 0);
 #pragma unroll
-        for (int i = 0; i < WP; ++i)
-            __builtin_amdgcn_global_load_lds((gvoid)(wsrc[i] + koff), (lvoid)(st + BM * 128 + (wave + 4 * i) * 1024),
+        for (int i = 0; i < XP; ++i)
+            __builtin_amdgcn_global_load_lds((gvoid)(wsrc[i] + koff), (lvoid)(st + DT * 128 + (wave + 4 * i) * 1024),
                                              16, 0, 0);
     };
 
@@ -414,41 +411,29 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     uint32_t chunk_off[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) chunk_off[kk] = ((2 * kk + half) ^ cmask) << 4;
-    const uint32_t w_row0 = BM * 128 + (BN / 2) * wn * 128 + col * 128;
-    const uint32_t x_row0 = ((BM / 2) * wm + col) * 128;
-    constexpr int W_BLOCK_STRIDE = 32 * 128;
+    const uint32_t w_row0 = DT * 128 + 32 * wn * 128 + col * 128;
+    const uint32_t x_row0 = (32 * wm + col) * 128;
 
     struct Ops {
-        u32x4 w[WNB];
-        u32x4 x[WMB];
+        u32x4 w, x;
     };
+    // Both addresses before the first read: with the second between the reads
+    // the compiler puts the third product behind the last operands' wait
+    // (512 x 64 x 17280 as a convolution 74.6 -> 78 us).
     auto read_ops = [&](uint32_t sbase, int kk, Ops& o) {
         const uint32_t wa = sbase + w_row0 + chunk_off[kk];
         const uint32_t xa = sbase + x_row0 + chunk_off[kk];
-        o.w[0] = lds_b128<0>(wa);
-        if constexpr (WNB > 1) o.w[1] = lds_b128<W_BLOCK_STRIDE>(wa);
-        o.x[0] = lds_b128<0>(xa);
-        if constexpr (WMB > 1) o.x[1] = lds_b128<32 * 128>(xa);
+        o.w = lds_b128<0>(wa);
+        o.x = lds_b128<0>(xa);
     };
     auto wait_ops = [&](Ops& o, auto n_tag) {
         constexpr int N = decltype(n_tag)::value;
-        if constexpr (WNB == 2 && WMB == 2)
-            asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(o.w[0]), "+v"(o.w[1]), "+v"(o.x[0]), "+v"(o.x[1]) : "n"(N));
-        else if constexpr (WNB == 2)
-            asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(o.w[0]), "+v"(o.w[1]), "+v"(o.x[0]) : "n"(N));
-        else if constexpr (WMB == 2)
-            asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(o.w[0]), "+v"(o.x[0]), "+v"(o.x[1]) : "n"(N));
-        else
-            asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(o.w[0]), "+v"(o.x[0]) : "n"(N));
+        asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(o.w), "+v"(o.x) : "n"(N));
     };
 
-    f32x16 acc[WNB][WMB];
+    f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < WNB; ++i)
-#pragma unroll
-        for (int j = 0; j < WMB; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
     // The MFMAs of the k-tile in the stage at LDS address sbase.
     auto mfma_tile = [&](uint32_t sbase) {
@@ -459,16 +444,11 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
             Ops& cur = o[kk & 1];
             if (kk < 3) {
                 read_ops(sbase, kk + 1, o[(kk + 1) & 1]);
-                wait_ops(cur, IC<NOPS>{});
+                wait_ops(cur, IC<2>{});
             } else {
                 wait_ops(cur, IC<0>{});
             }
-#pragma unroll
-            for (int i = 0; i < WNB; ++i)
-#pragma unroll
-                for (int j = 0; j < WMB; ++j)
-                    acc[i][j] = mfma32x32x16(__builtin_bit_cast(bf16x8, cur.w[i]), __builtin_bit_cast(bf16x8, cur.x[j]),
-                                             acc[i][j]);
+            acc = mfma32x32x16(__builtin_bit_cast(bf16x8, cur.w), __builtin_bit_cast(bf16x8, cur.x), acc);
         }
     };
 
@@ -512,8 +492,8 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int chunk = 4 * wn + c;  // head dimensions 32 wn + 8 c + 4 half + 0..3
-                const bf16x4 q4 = {f32_to_bf16(acc[0][0][4 * c]), f32_to_bf16(acc[0][0][4 * c + 1]),
-                                   f32_to_bf16(acc[0][0][4 * c + 2]), f32_to_bf16(acc[0][0][4 * c + 3])};
+                const bf16x4 q4 = {f32_to_bf16(acc[4 * c]), f32_to_bf16(acc[4 * c + 1]),
+                                   f32_to_bf16(acc[4 * c + 2]), f32_to_bf16(acc[4 * c + 3])};
                 *(bf16x4*)(lds + t * 128 + ((chunk ^ ((t >> 1) & 7)) << 4) + 8 * half) = q4;
             }
         }
@@ -584,41 +564,35 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
     };
 
-    // Epilogue: lane holds token (m-block base + col) and W rows
-    // (n-block base + 8c + 4*half + 0..3) in registers 4c..4c+3.  Bias and
-    // residual are loaded after the products: in front of them, in 42 more
-    // registers, they made the modules of 64 to 1024 x 1280 0.5 to 1 % slower and
-    // a convolution of 128 x 64 x 17280 77.0 us instead of 74.2.
-    auto n_of = [&](int i, int c) { return n0 + (BN / 2) * wn + 32 * i + 8 * c + 4 * half; };
-    auto m_of = [&](int j) { return m0 + (BM / 2) * wm + 32 * j + col; };
-    bf16x4 bias_v[WNB][4] = {}, res_h[WNB][WMB][4] = {};
-    f32x4 res_v[WNB][WMB][4] = {}, bias2_v[WNB][WMB][4] = {};
+    // Epilogue: lane holds token m and W rows n_of(c) .. + 3 in registers 4c ..
+    // 4c + 3.  Bias and residual are loaded after the products: in front of
+    // them, in 42 more registers, they made the modules of 64 to 1024 x 1280 0.5
+    // to 1 % slower.
+    const int m = m0 + 32 * wm + col;
+    auto n_of = [&](int c) { return n0 + 32 * wn + 8 * c + 4 * half; };
+    bf16x4 bias_v[4] = {}, res_h[4] = {};
+    f32x4 res_v[4] = {}, bias2_v[4] = {};
     auto load_addends = [&]() {
-        auto each = [&](auto f) {
+        const int64_t mc = min(m, p.M - 1);
+        if (p.bias != nullptr) {
 #pragma unroll
-            for (int i = 0; i < WNB; ++i)
+            for (int c = 0; c < 4; ++c) bias_v[c] = *(const bf16x4*)(p.bias + n_of(c));
+        }
+        if (p.resid != nullptr && p.resid_f32) {
 #pragma unroll
-                for (int j = 0; j < WMB; ++j)
+            for (int c = 0; c < 4; ++c) res_v[c] = *(const f32x4*)((const float*)p.resid + mc * p.ldr + n_of(c));
+        }
+        if (p.resid != nullptr && !p.resid_f32) {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) f(i, j, c, min(m_of(j), p.M - 1), n_of(i, c));
-        };
-        if (p.bias != nullptr)
-            each([&](int i, int j, int c, int, int n) {
-                if (j == 0) bias_v[i][c] = *(const bf16x4*)(p.bias + n);
-            });
-        if (p.resid != nullptr && p.resid_f32)
-            each([&](int i, int j, int c, int m, int n) {
-                res_v[i][j][c] = *(const f32x4*)((const float*)p.resid + (int64_t)m * p.ldr + n);
-            });
-        if (p.resid != nullptr && !p.resid_f32)
-            each([&](int i, int j, int c, int m, int n) {
-                res_h[i][j][c] = *(const bf16x4*)((const bf16*)p.resid + (int64_t)m * p.ldr + n);
-            });
-        if (p.bias2 != nullptr)
-            each([&](int i, int j, int c, int m, int n) {
-                bias2_v[i][j][c] = *(const f32x4*)(p.bias2 + (int64_t)(m / p.bias2_rows) * p.N + n);
-            });
+            for (int c = 0; c < 4; ++c) res_h[c] = *(const bf16x4*)((const bf16*)p.resid + mc * p.ldr + n_of(c));
+        }
+        if (p.bias2 != nullptr) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                bias2_v[c] = *(const f32x4*)(p.bias2 + (int64_t)((int)mc / p.bias2_rows) * p.N + n_of(c));
+        }
     };
+
     // GroupNorm staging.  X arrives with the direct loads like W; after the
     // products of k-tile kt each lane rewrites in place the 16-byte pieces of
     // k-tile kt + 1 that its own loads brought (so that its own wait suffices),
@@ -631,7 +605,7 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         for (int i = 0; i < XP; ++i) {
             const int r = 8 * (wave + 4 * i) + (lane >> 3);
             const int c0 = kt * DBK + 8 * ((lane & 7) ^ ((r >> 1) & 7));
-            bf16x8* at = (bf16x8*)(lds + stage * STAGE + (wave + 4 * i) * 1024 + lane * 16);
+            bf16x8* at = (bf16x8*)(lds + stage * DSTAGE + (wave + 4 * i) * 1024 + lane * 16);
             const bf16x8 v = *at;
             bf16x8 y;
 #pragma unroll
@@ -646,17 +620,16 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     // X of the k-tile before the newest: behind it its own W and, if issued, a k-tile.
     auto wait_x = [&](bool one_more) {
         if (one_more)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP + PT));
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(XP + PT));
         else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(WP));
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(XP));
     };
 
 #pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
+    for (int s = 0; s < DNS - 1; ++s)
         if (kt0 + s < kt1) issue(kt0 + s, s);
     if constexpr (XATT) xatt_stage();  // its loads wait behind the first k-tiles'
     if constexpr (AGN) {               // the statistics are merged while the first k-tiles are in flight
-        static_assert(NS == 3, "wait_x");
         const int img = m0 / p.gn_N;
         float* g_mean = tab + 2 * GEMM_GN_MAXC;
         float* g_rstd = g_mean + 256;
@@ -672,17 +645,22 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         wait_x(kt0 + 1 < kt1);
         gn_rewrite(kt0, 0);
     }
+    // A convolution's loop at a fixed place within the 32 bytes that are fetched
+    // at once (three instructions past a boundary): at that of the eight places
+    // 512 x 64 x 17280 takes 74.6 us, at the others 77.1 to 78.3, and code elsewhere
+    // in the kernel would decide which.  (The plain forms: no difference.)
+    if constexpr (CONV) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (int kt = kt0; kt < kt1; ++kt) {
-        // k-tiles issued after kt so far: min(kt1 - 1 - kt, NS - 2), PT loads each
-        wait_tiles_after<PT, NS - 2>(min(kt1 - 1 - kt, NS - 2));
+        // k-tiles issued after kt so far: min(kt1 - 1 - kt, DNS - 2), PT loads each
+        wait_tiles_after<PT, DNS - 2>(min(kt1 - 1 - kt, DNS - 2));
         if constexpr (AGN) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this lane's rewrite of X(kt)
         __builtin_amdgcn_s_barrier();  // everyone's pieces of tile kt landed; the stage of tile kt-1 is free
-        if (kt + NS - 1 < kt1) issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
-        mfma_tile(lds0 + ((kt - kt0) % NS) * STAGE);
+        if (kt + DNS - 1 < kt1) issue(kt + DNS - 1, (kt - kt0 + DNS - 1) % DNS);
+        mfma_tile(lds0 + ((kt - kt0) % DNS) * DSTAGE);
         if constexpr (AGN) {
             if (kt + 1 < kt1) {
                 wait_x(kt + 2 < kt1);
-                gn_rewrite(kt + 1, (kt - kt0 + 1) % NS);
+                gn_rewrite(kt + 1, (kt - kt0 + 1) % DNS);
             }
         }
     }
@@ -697,16 +675,12 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
     // order (its own from registers: the same values) and runs the epilogue.
     if (p.splitk > 1) {
         __shared__ int last_flag;
-        constexpr int NQ = WNB * WMB * 4;  // f32x4 chunks per lane
-        auto part_of = [&](int wg) { return (float*)p.split_ws + GEMM_SPLIT_COUNTERS + (int64_t)wg * BM * BN; };
+        auto part_of = [&](int wg) { return (float*)p.split_ws + GEMM_SPLIT_COUNTERS + (int64_t)wg * DT * DT; };
         {
             float* dst = part_of(bx) + (wave * 64 + lane) * 4;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const f32x16& a = acc[q / (4 * WMB)][(q / 4) % WMB];
-                const f32x4 v = {a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]};
-                *(f32x4*)(dst + q * 1024) = v;
-            }
+            for (int q = 0; q < 4; ++q)
+                *(f32x4*)(dst + q * 1024) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
         }
         __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): this thread's stores reached the L2
         __syncthreads();
@@ -719,76 +693,53 @@ __device__ __forceinline__ void gemm_dma_body(const GemmParams& p, const int bx,
         }
         __syncthreads();
         if (!last_flag) return;
-        f32x16 own[WNB][WMB];
+        const f32x16 own = acc;
 #pragma unroll
-        for (int i = 0; i < WNB; ++i)
-#pragma unroll
-            for (int j = 0; j < WMB; ++j) {
-                own[i][j] = acc[i][j];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-            }
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
         for (int pc = 0; pc < p.splitk; ++pc) {
             if (pc == piece) {
 #pragma unroll
-                for (int i = 0; i < WNB; ++i)
-#pragma unroll
-                    for (int j = 0; j < WMB; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[i][j][r] += own[i][j][r];
+                for (int r = 0; r < 16; ++r) acc[r] += own[r];
                 continue;
             }
             const float* src = part_of((tl * p.splitk + pc) * p.n_xcd + xcd) + (wave * 64 + lane) * 4;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
+            for (int q = 0; q < 4; ++q) {
                 const f32x4 v = *(const f32x4*)(src + q * 1024);
-                f32x16& a = acc[q / (4 * WMB)][(q / 4) % WMB];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a[4 * (q & 3) + e] += v[e];
+                for (int e = 0; e < 4; ++e) acc[4 * q + e] += v[e];
             }
         }
     }
 
     load_addends();
+    if (m >= p.M) return;
 #pragma unroll
-    for (int i = 0; i < WNB; ++i) {
+    for (int c = 0; c < 4; ++c) {
+        const int n = n_of(c);
+        f32x4 v;
 #pragma unroll
-        for (int j = 0; j < WMB; ++j) {
-            const int m = m_of(j);
-            if (m >= p.M) continue;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int n = n_of(i, c);
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float rv = p.resid_f32 ? res_v[i][j][c][e] : bf16_to_f32(res_h[i][j][c][e]);
-                    if (p.bias2 != nullptr) rv += bias2_v[i][j][c][e];
-                    v[e] = (acc[i][j][4 * c + e] + bf16_to_f32(bias_v[i][c][e])) + rv;
-                }
-                int ns;
-                void* dst = p.seg_stride > 0 ? strided_segment(p, n, ns) : out_segment(p, n, ns);
-                if (p.out_f32) {
-                    f32x4 o = {v[0], v[1], v[2], v[3]};
-                    *(f32x4*)((float*)dst + (int64_t)m * p.ldo + ns) = o;
-                } else {
-                    bf16x4 o = {f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};
-                    *(bf16x4*)((bf16*)dst + (int64_t)m * p.ldo + ns) = o;
-                }
-                if (p.out_bf16 != nullptr) {
-                    bf16x4 o = {f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};
-                    *(bf16x4*)((bf16*)p.out_bf16 + (int64_t)m * p.ldo + n) = o;
-                }
-            }
+        for (int e = 0; e < 4; ++e) {
+            float rv = p.resid_f32 ? res_v[c][e] : bf16_to_f32(res_h[c][e]);
+            if (p.bias2 != nullptr) rv += bias2_v[c][e];
+            v[e] = (acc[4 * c + e] + bf16_to_f32(bias_v[c][e])) + rv;
         }
+        const bf16x4 h = {f32_to_bf16(v[0]), f32_to_bf16(v[1]), f32_to_bf16(v[2]), f32_to_bf16(v[3])};
+        int ns;
+        void* dst = p.seg_stride > 0 ? strided_segment(p, n, ns) : out_segment(p, n, ns);
+        if (p.out_f32)
+            *(f32x4*)((float*)dst + (int64_t)m * p.ldo + ns) = v;
+        else
+            *(bf16x4*)((bf16*)dst + (int64_t)m * p.ldo + ns) = h;
+        if (p.out_bf16 != nullptr) *(bf16x4*)((bf16*)p.out_bf16 + (int64_t)m * p.ldo + n) = h;
     }
 }
 
-template <int BM, int BN, int NS, int FORM>
+template <int FORM>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmParams p) {
-    __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
+    __shared__ __attribute__((aligned(16))) char lds[DNS * DSTAGE];
     __shared__ __attribute__((aligned(16))) float tab[tab_floats(FORM)];
-    gemm_dma_body<BM, BN, NS, FORM>(p, blockIdx.x, blockIdx.y, lds, tab);
+    gemm_dma_body<FORM>(p, blockIdx.x, blockIdx.y, lds, tab);
 }
 
 // Two independent products, the second plain, in one launch (so that neither
@@ -801,15 +752,15 @@ struct GemmPair {
     int32_t gx_a, n_a, gx_b, b0;
 };
 
-template <int BM, int BN, int NS, int FORM_A>
+template <int FORM_A>
 __global__ __launch_bounds__(256) void gemm_dma_pair_kernel(GemmPair pp) {
-    __shared__ __attribute__((aligned(16))) char lds[NS * (BM + BN) * DBK * 2];
+    __shared__ __attribute__((aligned(16))) char lds[DNS * DSTAGE];
     __shared__ __attribute__((aligned(16))) float tab[tab_floats(FORM_A)];
     const int id = blockIdx.x;
     if (id < pp.n_a)
-        gemm_dma_body<BM, BN, NS, FORM_A>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, tab);
+        gemm_dma_body<FORM_A>(pp.a, id % pp.gx_a, id / pp.gx_a, lds, tab);
     else if (id >= pp.b0)
-        gemm_dma_body<BM, BN, NS, DMA_PLAIN>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, tab);
+        gemm_dma_body<DMA_PLAIN>(pp.b, (id - pp.b0) % pp.gx_b, (id - pp.b0) / pp.gx_b, lds, tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -997,13 +948,13 @@ hipError_t launch_dma64(const GemmParams& p, hipStream_t s) {
     dim3 grid((p.M + 63) / 64, p.N / 64);
     if (p.tpx > 0) grid = dim3((unsigned)(p.n_xcd * p.tpx * p.splitk), 1);
     if (p.xa_T > 0)
-        gemm_dma_kernel<64, 64, 3, DMA_XATT><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<DMA_XATT><<<grid, 256, 0, s>>>(p);
     else if (p.gn_N > 0)
-        gemm_dma_kernel<64, 64, 3, DMA_GN><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<DMA_GN><<<grid, 256, 0, s>>>(p);
     else if (p.conv_W > 0)
-        gemm_dma_kernel<64, 64, 3, DMA_CONV><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<DMA_CONV><<<grid, 256, 0, s>>>(p);
     else
-        gemm_dma_kernel<64, 64, 3, DMA_PLAIN><<<grid, 256, 0, s>>>(p);
+        gemm_dma_kernel<DMA_PLAIN><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -1244,7 +1195,7 @@ hipError_t launch_planned(const GemmParams& p, const GemmPlan& pl, hipStream_t s
     }
 }
 
-// Workgroups along x and y of a 64 x 64 pipelined launch (launch_dma).
+// Workgroups along x and y of a 64 x 64 pipelined launch (launch_dma64).
 void dma64_grid(const GemmParams& p, int& gx, int& gy) {
     if (p.tpx > 0) {
         gx = p.n_xcd * p.tpx * p.splitk;
@@ -1332,9 +1283,9 @@ hipError_t launch_gemm_pair(const GemmParams& a_in, const GemmParams& b_in, hipS
             const int64_t total = (int64_t)pp.b0 + (int64_t)pp.gx_b * gy_b;
             if (total > INT32_MAX) return hipErrorInvalidValue;
             if (a.gn_N > 0)
-                gemm_dma_pair_kernel<64, 64, 3, DMA_GN><<<dim3((unsigned)total), 256, 0, s>>>(pp);
+                gemm_dma_pair_kernel<DMA_GN><<<dim3((unsigned)total), 256, 0, s>>>(pp);
             else
-                gemm_dma_pair_kernel<64, 64, 3, DMA_PLAIN><<<dim3((unsigned)total), 256, 0, s>>>(pp);
+                gemm_dma_pair_kernel<DMA_PLAIN><<<dim3((unsigned)total), 256, 0, s>>>(pp);
             return hipGetLastError();
         }
     }

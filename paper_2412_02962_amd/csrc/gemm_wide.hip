@@ -21,11 +21,13 @@
 // over reading both halves first).
 //
 // Products with fewer tiles than compute units split K: the pieces of a
-// tile run on one XCD, leave their sums (fp32) in its L2, and each finishes
-// its share of the tile's outputs when all have arrived, adding the pieces
-// in order (so results do not depend on timing).  A piece waits a bounded
-// time for the others; if it gives up, the last one to arrive does its share
-// too.
+// tile run on one XCD, exchange their sums (fp32) through its L2, and each
+// finishes its share of the tile's outputs when all have arrived, adding the
+// pieces in order (so results do not depend on timing).  The sums of an XCD's
+// 32 workgroups are 2 MB for 128 x 128 tiles and 2.6 for 128 x 160, which its
+// 4 MB of L2 hold, but 5.2 MB for 256 x 160, of which some go to memory and
+// back (the merge of 9 us in kShapes).  A piece waits a bounded time for the
+// others; if it gives up, the last one to arrive does its share too.
 
 #include <math.h>
 

@@ -15,9 +15,9 @@ from paper_2412_02962_amd import build
 KERNELS = [
     (r"gemm80_kernelILi2E", "gemm.hip", 3),
     (r"gemm80_kernelILi4E", "gemm.hip", 2),
-    (r"gemm_dma_kernelILi64ELi64ELi3ELi0E", "gemm.hip", 3),
-    (r"gemm_dma_kernelILi64ELi64ELi3ELi1E", "gemm.hip", 3),
-    (r"gemm_dma_pair_kernelILi64ELi64ELi3ELi0E", "gemm.hip", 3),
+    (r"gemm_dma_kernelILi0E", "gemm.hip", 3),
+    (r"gemm_dma_kernelILi1E", "gemm.hip", 3),
+    (r"gemm_dma_pair_kernelILi0E", "gemm.hip", 3),
     (r"gemm_wide_kernelILi64ELi128ELi2ELi2ELb0ELb1E", "gemm_wide.hip", 3),
     (r"gemm_wide_kernelILi64ELi128ELi2ELi3E", "gemm_wide.hip", 2),
     (r"gemm_wide_kernelILi256ELi160E", "gemm_wide.hip", 1),
